@@ -230,3 +230,31 @@ def test_stencil_cache_block_sizes_and_chunks_same_bits(m, orc, node_dtype):
         got = run_gpu(m, g, z0, 0.02, 3000, 55.0, **kw)
         for x, y in zip(ref, got):
             assert np.array_equal(x, y), kw
+
+
+@pytest.mark.parametrize("nr,nth,n,block", [(4, 4, 1, 0), (5, 4, 64, 64), (9, 7, 65, 128), (33, 17, 257, 0),
+                                            (4, 33, 300, 256)])
+@pytest.mark.parametrize("f32", [False, True])
+def test_smallest_grids_and_ragged_blocks(m, orc, nr, nth, n, block, f32):
+    """Grids from the smallest that is accepted (one interior cell, whose stencil is the whole
+    grid) up, on which lanes change cell in r and theta or run off the interior, for batches
+    at the edges of a wavefront and of a block: parity with the oracle on the same nodes."""
+    st = [(1.0, 0.6)]
+    r0, width, th0 = 4.0, 40.0, 0.5
+    G = orc.grid_kerr(1.0, 0.6, nr, nth, r0, width / (nr - 1), th0, (math.pi - 2 * th0) / (nth - 1))
+    r_stop, r_esc = r0 + 1.02 * G.dr, r0 + (nr - 2.02) * G.dr
+    if f32:
+        G, g = f32_grids(orc, m, G, r_stop)
+    else:
+        g = gpu_grid_from(m, G, r_stop)
+    lo, hi = r0 + 1.1 * G.dr, r0 + (nr - 2.1) * G.dr
+    # the theta range of the interior, inside the sampler's own
+    t_in = th0 + 1.1 * G.dth
+    ranges = ((lo, hi), (max(t_in, 0.8), math.pi - max(t_in, 0.8))) + KERR_RANGES[2:]
+    rc, s0, _, _ = orc.ic_constants(96, st, n, ranges)
+    assert rc == 0
+    z0 = lower(orc, st, s0)
+    got = run_gpu(m, g, z0, 0.05, 400, r_esc, block=block)
+    ref = orc.integrate_grid(G, z0, 0.05, 400, r_stop=r_stop, r_escape=r_esc)
+    compare(orc, st, z0, *got, *ref,
+            lambda p0: orc.integrate_grid(G, p0, 0.05, 400, r_stop=r_stop, r_escape=r_esc))
