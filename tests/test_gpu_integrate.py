@@ -98,6 +98,39 @@ def test_init_strict_reports_exhausted_sampler(m, orc):
     assert rc2 == 0 and np.array_equal(att2.cpu().numpy(), att20)
 
 
+@pytest.mark.parametrize("n,max_att", [(1, 100000), (63, 100000), (65, 1), (4096, 64), (4097, 65), (5000, 100000),
+                                       (70001, 7), (1100003, 100000)])
+def test_init_sampler_runs_and_groups(m, orc, n, max_att):
+    """The sampler's wavefronts take a run of 1 to 256 lanes and put 1 to 64 threads on a
+    lane: batches at the edges of both, with attempt limits at the edges of a group of
+    threads, over spins with some invalid spacetime indices (NaN state, sampled as the
+    first spacetime).  Attempts and constants equal the oracle's exactly."""
+    import torch
+    st = [(1.0, 0.0), (1.0, 0.5), (1.0, 0.9)]
+    sol = np.arange(n, dtype=np.int32) % 3
+    sol_gpu = sol.copy()
+    sol_gpu[5::97] = 3
+    sol_gpu[7::97] = -1
+    bad = sol_gpu != sol
+    sol[bad] = 0
+    spec = m.ICSpec(mode=m.IC_CONSTANTS, seed=12, max_attempts=max_att)
+    state, consts, att = m.init_particles(spec, st, n, st_of_lane=torch.as_tensor(sol_gpu).cuda())
+    got, gc, ga = state.cpu().numpy(), consts.cpu().numpy(), att.cpu().numpy()
+    assert np.isnan(got[:, bad]).all()
+    for lo in sorted({0, max(0, n // 2 - 1500), max(0, n - 3000)}):
+        hi = min(n, lo + 3000)
+        rc, s0, c0, a0 = orc.ic_constants(12, st, hi - lo, KERR_RANGES, max_attempts=max_att,
+                                          st_of_lane=sol[lo:hi], lane0=lo)
+        s0[:, bad[lo:hi]] = np.nan
+        out = np.isnan(s0).all(axis=0)  # exhausted or invalid
+        assert np.array_equal(ga[lo:hi], a0)
+        ok = ~out
+        assert np.array_equal(gc[:, lo:hi][:, ok], c0[:, ok])
+        assert np.array_equal(np.isnan(got[:, lo:hi]), np.isnan(s0))
+        if ok.any():
+            assert mixed_rel(got[:, lo:hi][:, ok], s0[:, ok]).max() < 5e-13
+
+
 def test_init_circular_and_canonical_match_oracle(m, orc):
     import torch
     st = [(1.0, 0.0)]
