@@ -44,10 +44,10 @@ MAX_SPACETIMES = 64
 # FP64 flops of one RK4 step of one lane (static counts by csrc/flopcount.cpp:
 # add/sub/mul/div 1, fma 2, sincos 2).  Christoffel form: the work of a step is fixed
 # by its direct evaluation (kerr_accel_direct in csrc/kerr_accel.hpp: coefficients, then
-# the contraction), 514; the kernels evaluate the same acceleration regrouped, in 442
+# the contraction), 514; the FP64 kernels evaluate the same step regrouped, in 408
 # (FLOPS_PER_STEP_F64_KERNEL).  Hamilton's equations: 336.
 FLOPS_PER_STEP_F64 = 514
-FLOPS_PER_STEP_F64_KERNEL = 442
+FLOPS_PER_STEP_F64_KERNEL = 408
 FLOPS_PER_STEP_F64_HAM = 336
 # FP32-compensated steps (FP32 flops): the stage increment plus d + lo and a two-sum per
 # component (7 each); Christoffel form (direct evaluation, and as the kernel evaluates

@@ -8,8 +8,9 @@
 // sin/cos of a stage angle count 2 however the kernel obtains them (library sincos or
 // rotation).  The Christoffel form is counted twice: in its direct form
 // (kerr_accel_direct: the coefficients, then the contraction), which fixes the work of
-// one step for the roofline, and in the regrouped form the kernels evaluate
-// (kerr_accel), which needs fewer operations for the same acceleration.
+// one step for the roofline, and in the regrouped forms the kernels evaluate, which need
+// fewer operations for the same acceleration: kerr_accel_half with rk4_step_half in the
+// FP64 fixed-step kernels, kerr_accel in the FP32-compensated and the adaptive ones.
 //   g++ -O0 -std=c++17 flopcount.cpp -o flopcount && ./flopcount
 #include <cstdio>
 
@@ -52,6 +53,17 @@ struct AccelCount {
     }
 };
 
+struct AccelHalfCount {
+    Counted M, a;
+    void operator()(int, Counted r, Counted th, Counted ut, Counted ur, Counted uth, Counted uph,
+                    Counted &at2, Counted &ar, Counted &ath, Counted &aph2) const
+    {
+        g_flops += 2;  // sincos
+        const Counted s(std::sin(th.v)), c(std::cos(th.v));
+        malbec::kerr_accel_half<Counted>(M, a, r, s * s, s * c, ut, ur, uth, uph, at2, ar, ath, aph2);
+    }
+};
+
 struct HamCount {
     Counted M, a;
     malbec::HamConst<Counted> P;
@@ -74,11 +86,18 @@ void count_christoffel(const char *tag)
     Counted y[8] = {0.0, 7.0, 1.1, 0.0, 1.2, 0.1, 0.02, 0.05}, y1[8], sr[3];
     AccelCount<DIRECT> f{Counted(1.0), Counted(0.9)};
     Counted at, ar, ath, aph;
+    AccelHalfCount half{Counted(1.0), Counted(0.9)};
     g_flops = g_div = g_fma = g_addmul = 0;
-    f(0, y[1], y[2], y[4], y[5], y[6], y[7], at, ar, ath, aph);
+    if (DIRECT)
+        f(0, y[1], y[2], y[4], y[5], y[6], y[7], at, ar, ath, aph);
+    else
+        half(0, y[1], y[2], y[4], y[5], y[6], y[7], at, ar, ath, aph);
     long rhs = g_flops, rhs_div = g_div, rhs_fma = g_fma, rhs_am = g_addmul;
     g_flops = g_div = g_fma = g_addmul = 0;
-    malbec::rk4_step(f, Counted(0.02), y, y1, sr);
+    if (DIRECT)
+        malbec::rk4_step(f, Counted(0.02), y, y1, sr);
+    else
+        malbec::rk4_step_half(half, Counted(0.02), y, y1, sr);
     std::printf("rhs_flops%s %ld\nrhs_div%s %ld\nrhs_fma%s %ld\nrhs_addmul%s %ld\n", tag, rhs, tag,
                 rhs_div, tag, rhs_fma, tag, rhs_am);
     std::printf("step_flops%s %ld\nstep_fma%s %ld\nstep_addmul%s %ld\nstep_div%s %ld\n", tag,

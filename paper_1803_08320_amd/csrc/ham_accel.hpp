@@ -72,6 +72,37 @@ MALBEC_HD inline void kerr_ham(T M, T a, T r, T s, T c, T pr, T pth, const HamCo
     dpth = -fma(a2 * (s * c), twoH, hdthN) * irho2;
 }
 
+// The same right-hand side for the FP64 kernels, in s2 = sin^2 theta and sc = sin theta
+// cos theta, regrouped: with v = w / s = p_phi / s^2 + a p_t and D = P / Delta,
+//   w^2 = v (v s^2),  a s w = a (v s^2),  (1/2) d_theta N = s c v (2 a p_t - v),
+//   r N / rho^2 - (1/2) d_r N = r (N / rho^2 + 2 D p_t) - (r - M)(p_r^2 + D^2).
+// 44 instructions where kerr_ham takes 53.
+template <typename T>
+MALBEC_HD inline void kerr_ham_s2(T M, T a, T r, T s2, T sc, T pr, T pth, const HamConst<T> &P, T &dt,
+                                  T &dr, T &dth, T &dph, T &dpr, T &dpth)
+{
+    const T a2 = a * a;
+    const T A = fma(r, r, a2);               // r^2 + a^2
+    const T rho2 = fma(-a2, s2, A);          // r^2 + a^2 cos^2
+    const T Delta = fma(-(M + M), r, A);     // r^2 - 2 M r + a^2
+    const T Ds2 = Delta * s2;
+    const T inv = recip(rho2 * Ds2);         // 1 / (rho^2 Delta s^2)
+    const T irho2 = inv * Ds2;
+    const T iDs2 = inv * rho2;
+    const T D = fma(A, P.pt, P.apph) * (iDs2 * s2);  // P / Delta
+    const T v = fma(P.pph, iDs2 * Delta, P.apt);     // w / s
+    const T g = v * s2;                              // w s
+    const T prpr = pr * pr, DD = D * D;
+    const T N = fma(v, g, fma(Delta, prpr - DD, pth * pth));  // P^2 / Delta = Delta D^2
+    const T twoH = N * irho2;                // g^{mu nu} p_mu p_nu
+    dr = (Delta * irho2) * pr;
+    dth = pth * irho2;
+    dt = fma(a, g, -(A * D)) * irho2;
+    dph = fma(-a, D, v) * irho2;
+    dpr = fma(r, fma(P.pt + P.pt, D, twoH), -((r - M) * (prpr + DD))) * irho2;
+    dpth = -(fma(a2, twoH, v * fma(T(2), P.apt, -v)) * (irho2 * sc));
+}
+
 // Stages of one classic RK4 step (b = 1/6, 1/3, 1/3, 1/6; c = 0, 1/2, 1/2, 1) of the
 // canonical state z = (t, r, theta, phi, p_t, p_r, p_theta, p_phi).
 // f(stage, r, theta, p_r, p_theta, dt, dr, dth, dph, dpr, dpth) evaluates the

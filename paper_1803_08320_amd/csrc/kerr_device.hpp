@@ -234,6 +234,21 @@ struct AccelF64T {
 };
 using AccelF64 = AccelF64T<StageTrig>;
 
+// The same with half of a^t and a^phi (kerr_accel_half), for rk4_step_half.
+template <typename Trig>
+struct AccelHalfF64T {
+    double M, a;
+    Trig trig;
+    __device__ __forceinline__ void operator()(int stage, double r, double th, double ut, double ur,
+                                               double uth, double uph, double &at2, double &ar,
+                                               double &ath, double &aph2)
+    {
+        double s, c;
+        trig(stage, th, s, c);
+        kerr_accel_half<double>(M, a, r, s * s, s * c, ut, ur, uth, uph, at2, ar, ath, aph2);
+    }
+};
+
 // One FP64 RK4 step (Christoffel form).  SHORT = true for the fixed-step integrators
 // (small stage offsets), false for steps whose stage points move further (the camera's
 // h = h0 max(1, r / h_r0)).  Tab: where the trigonometry table is read from.
@@ -241,12 +256,23 @@ template <bool SHORT = true, typename Tab = TabGlobal>
 __device__ __forceinline__ void rk4_step_f64(const Spacetime &S, double h, const double y[8],
                                              double y1[8], double sr[3])
 {
-    AccelF64T<StageTrigT<SHORT, Tab>> f{S.M, S.a, {}};
+    AccelHalfF64T<StageTrigT<SHORT, Tab>> f{S.M, S.a, {}};
+    rk4_step_half(f, h, y, y1, sr);
+}
+
+// One FP64 RK4 step on kerr_accel, the acceleration that the FP32 stages of the compensated
+// integrator evaluate (its FP64 zone).
+__device__ __forceinline__ void rk4_step_f64_zone(const Spacetime &S, double h, const double y[8],
+                                                  double y1[8], double sr[3])
+{
+    AccelF64T<StageTrigT<true>> f{S.M, S.a, {}};
     rk4_step(f, h, y, y1, sr);
 }
 
-// FP64 canonical right-hand side (Hamiltonian form) as a functor for rk4_ham_step.
-template <typename Trig>
+// FP64 canonical right-hand side (Hamiltonian form) as a functor for rk4_ham_step.  S2: the
+// form of the FP64 kernels (kerr_ham_s2), else the one that the FP32 stages of the
+// compensated integrator evaluate (kerr_ham).
+template <typename Trig, bool S2 = true>
 struct HamF64T {
     double M, a;
     const HamConst<double> &P;
@@ -257,7 +283,10 @@ struct HamF64T {
     {
         double s, c;
         trig(stage, th, s, c);
-        kerr_ham<double>(M, a, r, s, c, pr, pth, P, dt, dr, dth, dph, dpr, dpth);
+        if (S2)
+            kerr_ham_s2<double>(M, a, r, s * s, s * c, pr, pth, P, dt, dr, dth, dph, dpr, dpth);
+        else
+            kerr_ham<double>(M, a, r, s, c, pr, pth, P, dt, dr, dth, dph, dpr, dpth);
     }
 };
 
@@ -266,6 +295,15 @@ __device__ __forceinline__ void rk4_step_ham_f64(const Spacetime &S, const HamCo
                                                  double sr[3])
 {
     HamF64T<StageTrigT<true>> f{S.M, S.a, P, {}};
+    rk4_ham_step(f, h, z, z1, sr);
+}
+
+// One FP64 step of the compensated integrator's FP64 zone.
+__device__ __forceinline__ void rk4_step_ham_f64_zone(const Spacetime &S, const HamConst<double> &P,
+                                                      double h, const double z[8], double z1[8],
+                                                      double sr[3])
+{
+    HamF64T<StageTrigT<true>, false> f{S.M, S.a, P, {}};
     rk4_ham_step(f, h, z, z1, sr);
 }
 
@@ -294,19 +332,29 @@ __device__ __forceinline__ int32_t terminate_f64(const Spacetime &S, double r_es
 }
 
 // The common outcome of terminate_f64 tested first: true only when it would return
-// kActive with y1 accepted (every stage radius above r_stop, y1's r inside
-// (r_stop, r_escape) and theta inside (0, pi), which rule out a NaN there, and the
-// other six components finite).  When it returns false (a NaN stage radius included)
-// the caller applies terminate_f64, which may still give kActive.
+// kActive with y1 accepted.  The tests read the high words of the doubles, as integers
+// (for r and theta: a positive double orders as its bits, and a NaN's high word is above
+// every finite one's or negative) and, for the other components, as single-precision
+// numbers, where the high word of an infinite or NaN double, and of a finite one above
+// 2^1017, is a NaN.  They are strict on the high words, so a value within a high word
+// (2^-20 relative) of a limit fails: when the result is false (a NaN stage radius
+// included) the caller applies terminate_f64, which may still give kActive.  A NaN stage
+// radius with a positive sign passes the first test, but then the stage's velocities, and
+// with them y1's, are NaN.  Nine 32-bit instructions, which issue at twice the rate of
+// FP64 ones, instead of 13 FP64 compares (measured with the regrouped step: kernels in
+// integrate.hip).
 __device__ __forceinline__ bool still_active_f64(const Spacetime &S, double r_escape,
                                                  const double sr[3], const double y1[8])
 {
-    bool ok = sr[0] > S.r_stop && sr[1] > S.r_stop && sr[2] > S.r_stop;
-    ok = ok && y1[1] > S.r_stop && y1[1] < r_escape;
-    ok = ok && y1[2] > 0.0 && y1[2] < 3.14159265358979323846;
-    ok = ok && __builtin_isfinite(y1[0]) && __builtin_isfinite(y1[3]);
-#pragma unroll
-    for (int k = 4; k < 8; ++k) ok = ok && __builtin_isfinite(y1[k]);
+    auto hi = [](double x) { return (int32_t)__double2hiint(x); };
+    auto hf = [](double x) { return __int_as_float((int32_t)__double2hiint(x)); };
+    const int32_t r_lo = min(min(hi(sr[0]), hi(sr[1])), min(hi(sr[2]), hi(y1[1])));
+    bool ok = (r_lo > hi(S.r_stop)) & (hi(y1[1]) < hi(r_escape));
+    // theta in (0, pi): its high word in [1, that of pi)
+    ok &= (uint32_t)(hi(y1[2]) - 1) < 0x400921FBu - 1u;
+    ok &= !__builtin_isunordered(hf(y1[0]), hf(y1[3]));
+    ok &= !__builtin_isunordered(hf(y1[4]), hf(y1[5]));
+    ok &= !__builtin_isunordered(hf(y1[6]), hf(y1[7]));
     return ok;
 }
 

@@ -175,9 +175,9 @@ struct MixProg {
 #pragma unroll
             for (int c = 0; c < 8; ++c) y[c] = (double)L.hi[c] + (double)L.lo[c];
             if (HAM)
-                rk4_step_ham_f64(S, L.P64, A.h, y, y1, sr);
+                rk4_step_ham_f64_zone(S, L.P64, A.h, y, y1, sr);
             else
-                rk4_step_f64(S, A.h, y, y1, sr);
+                rk4_step_f64_zone(S, A.h, y, y1, sr);
             bool accept;
             L.st = terminate_f64(S, A.r_escape, sr, y1, accept);
             // a step that is not accepted ends the lane (HORIZON at a stage point, or

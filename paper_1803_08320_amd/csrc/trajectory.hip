@@ -45,6 +45,8 @@ __device__ __forceinline__ int32_t rec_step(const RecArgs &A, const Spacetime &S
         rk4_step_ham_f64(S, P, A.h, y, y1, sr);
     else
         rk4_step_f64(S, A.h, y, y1, sr);
+    accept = true;  // the common outcome of the stop rules first
+    if (still_active_f64(S, A.r_escape, sr, y1)) return kActive;
     return terminate_f64(S, A.r_escape, sr, y1, accept);
 }
 

@@ -389,3 +389,40 @@ def test_largest_batch_indexing(m, orc):
         assert np.array_equal(x, y)
     ref = orc.integrate(st, s0, 0.02, 40)
     compare(orc, st, s0, *outs[0][:3], *ref, oracle_rerun(orc, st, 0.02, 40))
+
+
+@pytest.mark.parametrize("form", ["christoffel", "hamiltonian"])
+def test_stop_rules_next_to_their_limits(m, orc, form):
+    """The kernels test the usual outcome on the high words of the doubles and fall back to
+    the full rule within 2^-20 of a limit: results on both sides of r_escape, of the stop
+    radius and of theta = 0 and pi, from 1e-12 to 1e-5 away, in the same high word as the
+    limit and in the next, stop (or not) exactly as the oracle's."""
+    ham = form == "hamiltonian"
+    st, h = [(1.0, 0.0)], 1e-3
+    off = np.array([s * 10.0 ** -k for k in range(5, 13) for s in (1, -1)])
+    r_esc, r_stop = 20.0, 1.25 * 2.0
+
+    def states(r, th, ur, uth):
+        n = len(off)
+        y = np.zeros((8, n))
+        y[1], y[2], y[5], y[6] = r, th, ur, uth
+        f = 1.0 - 2.0 / y[1]
+        y[4] = np.sqrt((1.0 + y[5] ** 2 / f + (y[1] * y[6]) ** 2) / f)
+        if ham:  # Schwarzschild: lower the index
+            y[4], y[5], y[6] = -f * y[4], y[5] / f, y[1] ** 2 * y[6]
+        return y
+
+    # one step moves by h u: aim the result of the second step at the limit plus off
+    s0 = np.concatenate([states(r_esc * (1 + off) - 2 * h * 0.3, 1.2, 0.3, 0.0),
+                         states(r_stop * (1 + off) + 2 * h * 0.1, 1.2, -0.1, 0.0),
+                         states(10.0, np.pi * (1 + off) - 2 * h * 0.01, 0.0, 0.01),
+                         states(10.0, off + 2 * h * 0.01, 0.0, -0.01),
+                         states(10.0, 1.0, 0.0, 0.0)], axis=1)
+    kw = dict(horizon_factor=1.25, r_escape=r_esc)
+    got = run_gpu(m, st, s0, h, 3, formulation=form, **kw)
+    ref = orc.integrate(st, s0, h, 3, hamiltonian=ham, **kw)
+    assert np.array_equal(got[1], ref[1]) and np.array_equal(got[2], ref[2])
+    n = len(off)
+    for j, want in enumerate((2, 1, 4, 4)):  # the lanes meet their limits
+        assert (ref[1][j * n:(j + 1) * n] == want).sum() >= n // 3, (j, ref[1][j * n:(j + 1) * n])
+    assert (ref[1][4 * n:] == 0).all()
