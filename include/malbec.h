@@ -92,7 +92,7 @@ extern "C" {
 
 /* Work order of the persistent adaptive kernel (malbec_adaptive.schedule). */
 #define MALBEC_SCHED_INDEX 0      /* lanes in index order */
-#define MALBEC_SCHED_PERIAPSIS 1  /* smallest periapsis first (malbec_adaptive_order) */
+#define MALBEC_SCHED_PERIAPSIS 1  /* lanes expected to take most attempts first */
 #define MALBEC_SCHED_BUCKETS 1024 /* keys of malbec_adaptive_order: 0 .. 1023 */
 #define MALBEC_NOALLOC_MAX_LANES 2097152 /* batch limit of malbec_integrate_adaptive_noalloc */
 
@@ -170,7 +170,8 @@ typedef struct {
     int32_t persistent;    /* 1: work-queue kernel (lanes need different attempt counts) */
     int32_t steps_per_chunk; /* persistent: attempts between retire/refill checks, 0 = 8 */
     int32_t schedule;      /* persistent: MALBEC_SCHED_INDEX (0) or MALBEC_SCHED_PERIAPSIS
-                              (hand out the lanes in the order of malbec_adaptive_order);
+                              (the lanes expected to take most attempts first, from the
+                              radial motion, and so the closest passages, until tau_end);
                               the results do not depend on it */
 } malbec_adaptive;
 
@@ -356,9 +357,10 @@ MALBEC_API int malbec_integrate_adaptive(const malbec_adaptive *ad, const malbec
                                          int32_t *status, int32_t *steps, int32_t *rejects,
                                          void *ws, size_t ws_bytes, void *stream);
 
-/* Work order for the persistent adaptive kernel (ad->schedule = MALBEC_SCHED_PERIAPSIS
- * computes it in its workspace; this entry point exposes it).  Not an operation of the
- * paper: a schedule.  An adaptive integrator takes most of its attempts near the
+/* A work order for adaptive integration: the lanes by the periapsis of their geodesic.
+ * (ad->schedule = MALBEC_SCHED_PERIAPSIS follows the radial motion further, through every
+ * passage until tau_end, in the same workspace.)  Not an operation of the paper: a
+ * schedule.  An adaptive integrator takes most of its attempts near the
  * orbit's closest approach, and a long lane handed out last keeps its wavefront busy
  * after the queue has drained, so the lanes expected to be longest go first.  The
  * expectation is ranked by the periapsis r_p of the lane's geodesic: the first zero,

@@ -380,8 +380,8 @@ def integrate_adaptive(state: torch.Tensor, tau: torch.Tensor, h: torch.Tensor,
                        ws: Optional[torch.Tensor] = None, schedule: Optional[str] = None):
     """Dormand-Prince 5(4) with per-lane step size up to tau_end; state[8, n], tau and h
     (float64[n]), status, steps and rejects (int32[n]) in/out.  schedule: "index" or
-    "periapsis" (persistent only: lanes handed out smallest periapsis first; the results
-    are the same); None = "periapsis" for a persistent launch, else "index"."""
+    "periapsis" (persistent only: the lanes expected to take most attempts, from their
+    radial motion until tau_end, are handed out first; the results are the same); None = "periapsis" for a persistent launch, else "index"."""
     n = state.shape[-1]
     if schedule is None:
         schedule = "periapsis" if persistent else "index"
@@ -460,7 +460,7 @@ class Grid:
 
 def adaptive_order(state: torch.Tensor, tau: torch.Tensor, status: torch.Tensor, spacetimes,
                    tau_end: float, st_of_lane: Optional[torch.Tensor] = None):
-    """The persistent adaptive kernel's periapsis work order: returns (order, keys), both
+    """The lanes in the order of their periapsis: returns (order, keys), both
     int32[n] on the device holding uint32 values (see malbec_adaptive_order)."""
     n = state.shape[-1]
     b = _Batch(_spacetimes(spacetimes), st_of_lane, n)

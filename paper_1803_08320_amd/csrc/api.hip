@@ -347,7 +347,7 @@ int malbec_integrate_adaptive(const malbec_adaptive *ad, const malbec_batch *b, 
         void *sw = (char *)ws + 256;
         uint32_t *o = (uint32_t *)((char *)sw + sched_layout(n).order);
         rc = launch_adaptive_order(T, b->st_of_lane, n, state, tau, status, ad->tau_end, o,
-                                   nullptr, sw, (hipStream_t)stream);
+                                   nullptr, sw, (hipStream_t)stream, &ad->r_escape);
         if (rc) return rc;
         order = o;
     }

@@ -82,11 +82,12 @@ struct SchedLayout {
     size_t count, next, key, order, bytes;
 };
 SchedLayout sched_layout(int64_t n);
-// keys: nullptr = in the workspace.
+// keys: nullptr = in the workspace.  by_cost_r_escape: nullptr = the order by periapsis; else
+// the order by expected length, longest first, of lanes that also stop at this radius.
 int launch_adaptive_order(const StTable &T, const int32_t *st_of_lane, int64_t n,
                           const double *state, const double *tau, const int32_t *status,
                           double tau_end, uint32_t *order, uint32_t *keys, void *ws,
-                          hipStream_t s);
+                          hipStream_t s, const double *by_cost_r_escape = nullptr);
 int launch_grid_fill_kerr(const malbec_grid &g, double M, double a, void *nodes, hipStream_t s);
 int launch_integrate_grid(const malbec_run &run, const malbec_grid &g, int64_t n, double *state,
                           int32_t *status, int32_t *steps, hipStream_t s);

@@ -341,3 +341,28 @@ def test_periapsis_key_brackets_the_closest_approach(m, orc):
     hi = rp * 2.0 ** ((k + 1) / 32.0)
     assert np.all(lo[bound] < rmin[bound]), np.c_[lo, rmin, hi][bound][:5]
     assert np.all(rmin[bound] <= hi[bound] * 1.002), np.c_[lo, rmin, hi][bound][:5]
+
+
+@pytest.mark.parametrize("n,tau_end", [(1, 300.0), (257, 1e-3), (700, 2000.0)])
+def test_length_order_of_unusual_lanes(m, orc, n, tau_end):
+    """The estimate behind the work order meets plunging, escaping, null, unbound and unusable
+    lanes, other masses, a tau_end below the first step and one beyond the steps it follows:
+    every lane is handed out once and the results are bitwise those of the index order."""
+    sts = [(1.0, 0.9), (2.5, 0.0), (1e-3, 1e-3)]
+    sol = (np.arange(n) % 3).astype(np.int32)
+    rc, s0, _, _ = orc.ic_constants(93, sts[:1], n, KERR_RANGES)
+    M = np.array([x[0] for x in sts])[sol]
+    s0[1] *= M
+    s0[6:] /= M
+    s0[5, 3::7] *= -40.0                   # inward or outward at high speed (norm not kept)
+    s0[4:, 4::11] = [[1.4], [0.2], [0.0], [0.0]]
+    s0[5, 6::50] = np.nan
+    s0[1, 9::60] = 0.5 * M[9::60]          # inside the horizon
+    status, tau0 = np.zeros(n, np.int32), np.zeros(n)
+    kw = dict(r_escape=60.0, max_attempts=3000)
+    a = run_lanes(m, sts, s0, status, tau0, tau_end, sol, persistent=True, schedule="index", **kw)
+    b = run_lanes(m, sts, s0, status, tau0, tau_end, sol, persistent=True, schedule="periapsis", **kw)
+    for x, y in zip(a, b):
+        assert np.array_equal(x, y, equal_nan=x.dtype.kind == "f")
+    if n > 500:
+        assert len(np.unique(a[3])) >= 4   # several ways of ending are among them
