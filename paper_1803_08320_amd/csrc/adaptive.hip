@@ -59,7 +59,7 @@ __device__ __forceinline__ double rpow5(double err)
 using AccelAd = AccelF64T<StageTrigT<false, TabLds>>;
 
 struct AdProg {
-    const AdArgs &A;
+    const AdArgs &A;         // the controls, used in every attempt
     const Spacetime *table;  // LDS copy of the spacetimes (mixed batch)
     bool multi;
     int32_t n_st;
@@ -80,29 +80,44 @@ struct AdProg {
         f(0, L.y[1], L.y[2], L.y[4], L.y[5], L.y[6], L.y[7], L.k1a[0], L.k1a[1], L.k1a[2],
           L.k1a[3]);
     }
-    __device__ __forceinline__ int64_t lane_of(int64_t item) const
+    // The arrays' addresses are read from the kernel's arguments again where a lane is taken or
+    // stored: kept in scalar registers across the attempts, they pushed the controls and the
+    // tableau's constants out into vector lanes (113 v_readlane in the kernel, most of them in
+    // the attempt; 36 now: to tau = 400 at a tolerance of 1e-12, 65,536 lanes 4.53 -> 4.34 ms,
+    // 262,144 lanes 5.21 -> 5.06, 1,048,576 lanes 13.94 -> 13.83).  AdArgs is the kernels' first
+    // argument.
+    typedef const __attribute__((address_space(4))) AdArgs *Args;
+    __device__ static __forceinline__ Args args()
     {
-        return A.order ? (int64_t)A.order[item] : item;
+        Args p = (Args)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(p));
+        return p;
+    }
+    __device__ static __forceinline__ int64_t lane_of(Args A, int64_t item)
+    {
+        const uint32_t *order = A->order;
+        return order ? (int64_t)order[item] : item;
     }
     __device__ __forceinline__ bool load(int64_t item, Lane &L)
     {
-        const int64_t i = lane_of(item);
-        L.st = A.status[i];
+        const Args A = args();
+        const int64_t i = lane_of(A, item);
+        L.st = A->status[i];
         if (L.st != kActive) return false;
         int32_t sid = 0;
         if (multi) {
-            sid = A.st_of_lane[i];
+            sid = A->st_of_lane[i];
             if (sid < 0 || sid >= n_st) {
-                A.status[i] = kNonfinite;
+                A->status[i] = kNonfinite;
                 return false;
             }
         }
         L.sid = sid;
-        L.tau = A.tau[i];
-        if (!(L.tau < A.tau_end)) return false;
+        L.tau = A->tau[i];
+        if (!(L.tau < A->tau_end)) return false;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) L.y[k] = A.state[k * A.n + i];
-        L.h = A.h[i];
+        for (int k = 0; k < 8; ++k) L.y[k] = A->state[k * A->n + i];
+        L.h = A->h[i];
         L.capped = false;
         L.acc = 0;
         L.rej = 0;
@@ -177,14 +192,15 @@ struct AdProg {
     {
         // the index is laundered so that the addresses of the loads are not kept
         // live across the attempts for reuse here
-        const int64_t i = lane_of(opaque(item));
+        const Args A = args();
+        const int64_t i = lane_of(A, opaque(item));
 #pragma unroll
-        for (int k = 0; k < 8; ++k) A.state[k * A.n + i] = L.y[k];
-        A.tau[i] = L.tau;
-        A.h[i] = L.h;
-        A.status[i] = L.st;
-        A.steps[i] += L.acc;
-        A.rejects[i] += L.rej;
+        for (int k = 0; k < 8; ++k) A->state[k * A->n + i] = L.y[k];
+        A->tau[i] = L.tau;
+        A->h[i] = L.h;
+        A->status[i] = L.st;
+        A->steps[i] += L.acc;
+        A->rejects[i] += L.rej;
     }
 };
 
