@@ -17,7 +17,9 @@ namespace malbec {
 //   bool load(int64_t item, Lane&)   -- false: nothing to do for this item
 //   bool step(Lane&)                 -- one step; true when the item is finished
 //   void store(int64_t item, const Lane&)
-template <class Prog>
+// or, with RUNS, in place of step
+//   bool run(Lane&, int32_t n)       -- up to n steps; true when the item is finished
+template <bool RUNS = false, class Prog>
 __device__ __forceinline__ void persistent_loop(Prog &P, int64_t n_items,
                                                 unsigned long long *counter, int32_t chunk)
 {
@@ -46,7 +48,12 @@ __device__ __forceinline__ void persistent_loop(Prog &P, int64_t n_items,
         }
         const bool busy = __ballot(item >= 0) != 0ull;
         if (!busy && !open) break;
-        if (item >= 0) {
+        if constexpr (RUNS) {
+            if (item >= 0 && P.run(L, chunk)) {
+                P.store(item, L);
+                item = -1;
+            }
+        } else if (item >= 0) {
             for (int32_t s = 0; s < chunk; ++s) {
                 if (P.step(L)) {
                     P.store(item, L);

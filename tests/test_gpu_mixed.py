@@ -288,3 +288,46 @@ def test_mixed_full_size_sampled(m, orc):
     assert np.quantile(dE, 0.99) < F32K_DE_P99
     assert np.quantile(dQ, 0.99) < F32K_DQ_P99
     assert np.quantile(pos, 0.99) < F32K_POS_P99
+
+
+@pytest.mark.parametrize("form", ["christoffel", "hamiltonian"])
+@pytest.mark.parametrize("persistent", [False, True])
+def test_steps_in_pairs_next_to_the_limits(m, orc, form, persistent):
+    """A launch that takes FP32 steps in pairs, under single-precision tests, gives the bits
+    of one that hands out single steps, which take the full rules: lanes within an ulp or a
+    step of the FP64 zone, of the escape radius and of the poles, lanes that plunge, and
+    lanes that are not finite; odd and even numbers of steps."""
+    import torch
+    st = [(1.0, 0.9), (1.0, 0.0)]
+    n = 640
+    rng = np.random.default_rng(5)
+    _, s0, _, _ = orc.ic_constants(21, [st[0]], n, KERR_RANGES)
+    s0 = np.ascontiguousarray(s0)
+    zone, escape = 1.5 * (1.0 + math.sqrt(1.0 - 0.81)), 60.0
+    for lo, r in ((0, zone), (128, escape)):
+        s0[1, lo:lo + 128] = r
+        s0[5, lo:lo + 128] = rng.uniform(-1.0, 1.0, 128)
+        s0[1, lo:lo + 64] *= 1.0 + np.float64(2.0) ** rng.integers(-50, -4, 64) * rng.choice([-1, 1], 64)
+    s0[2, 256:288] = 10.0 ** rng.uniform(-6.0, -1.0, 32)
+    s0[2, 288:320] = math.pi - 10.0 ** rng.uniform(-6.0, -1.0, 32)
+    s0[5, 320:400] = -rng.uniform(2.0, 60.0, 80)
+    for i, v in enumerate((math.nan, math.inf, -math.inf, 1e39, 1e300, -1.0, 0.0, 1e-46)):
+        for c in range(8):
+            s0[c, 400 + 8 * i + c] = v
+    sol = (np.arange(n) % 2).astype(np.int32)
+    kw = dict(precision="f32k", formulation=form, fp64_zone_factor=1.5, r_escape=escape)
+
+    def go(n_steps, persistent, steps_per_chunk):
+        state = torch.as_tensor(s0).cuda()
+        status = torch.zeros(n, dtype=torch.int32, device="cuda")
+        steps = torch.zeros(n, dtype=torch.int32, device="cuda")
+        m.integrate(state, status, steps, st, h=0.05, n_steps=n_steps, persistent=persistent,
+                    st_of_lane=torch.as_tensor(sol).cuda(), steps_per_chunk=steps_per_chunk, **kw)
+        return state.cpu().numpy(), status.cpu().numpy(), steps.cpu().numpy()
+
+    for n_steps in (1, 2, 3, 40, 41):
+        got, ref = go(n_steps, persistent, 0), go(n_steps, True, 1)
+        np.testing.assert_array_equal(got[0], ref[0])  # NaN equals NaN here, no tolerance
+        np.testing.assert_array_equal(got[1], ref[1])
+        np.testing.assert_array_equal(got[2], ref[2])
+    assert set(np.unique(got[1])) >= {0, 1, 2, 4}
