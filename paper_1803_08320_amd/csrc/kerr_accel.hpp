@@ -272,6 +272,42 @@ MALBEC_HD inline void kerr_accel_half(T M, T a, T r, T s2, T sc, T ut, T ur, T u
     ath = fma(-sig2, uth, fma(sc, fma(DI, uu, q * (zeta * zeta)), -(k1 * N)));
 }
 
+// kerr_accel_half at a = 0 (Schwarzschild): the terms that are then zero are left out and
+// every other is rounded as there, so finite results are the same bits.  48 instructions where
+// kerr_accel_half takes 60.
+template <typename T>
+MALBEC_HD inline void schwarzschild_accel_half(T M, T r, T s2, T sc, T ut, T ur, T uth, T uph,
+                                               T &at2, T &ar, T &ath, T &aph2)
+{
+    const T r2 = r * r;
+    const T M2 = M + M;
+    const T Delta = fma(-M2, r, r2);        // r^2 - 2 M r
+    const T Ds2 = Delta * s2;
+    const T inv = recip(r2 * Ds2);          // 1 / (r^2 Delta s^2)
+    const T ir2 = inv * Ds2;                // 1 / r^2
+    const T iDs2 = inv * r2;                // 1 / (Delta s^2)
+    const T iDelta = iDs2 * s2;             // 1 / Delta
+    const T cot = (iDs2 * sc) * Delta;
+    const T DI = Delta * ir2;
+    const T ri = r * ir2;                   // 1 / r
+    const T q = M2 * ri;                    // 2 M / r
+    const T q_r = fma(-q, ri, M * ir2);     // (1/2) d_r q
+
+    const T HV = q_r * ut;
+    const T ru = r * uph;
+    const T qru = q * ru;
+    const T urD = ur * iDelta;
+    at2 = urD * (r2 * HV);
+    aph2 = fma(uth, cot * -uph, urD * (qru - ru));
+
+    const T sigma = ri * ur;
+    const T sig2 = sigma + sigma;
+    const T N = fma(ur, urD, uth * uth);
+    const T uu = uph * uph;
+    ar = fma(DI, fma(ut, HV, r * fma(s2, uu, N)), ur * fma(r - M, urD, -sig2));
+    ath = fma(-sig2, uth, sc * fma(DI, uu, q * uu));
+}
+
 // Reverse mode of kerr_accel: given the cotangents (bat, bar, bath, baph) of
 // (a^t, a^r, a^theta, a^phi), the cotangents of r, s = sin theta, c = cos theta and
 // of the 4-velocity (ub[0..3] for u^t, u^r, u^theta, u^phi), i.e. the transposed

@@ -234,8 +234,8 @@ struct AccelF64T {
 };
 using AccelF64 = AccelF64T<StageTrig>;
 
-// The same with half of a^t and a^phi (kerr_accel_half), for rk4_step_half.
-template <typename Trig>
+// The same with half of a^t and a^phi (kerr_accel_half), for rk4_step_half.  ZERO_A: a = 0.
+template <typename Trig, bool ZERO_A = false>
 struct AccelHalfF64T {
     double M, a;
     Trig trig;
@@ -245,18 +245,21 @@ struct AccelHalfF64T {
     {
         double s, c;
         trig(stage, th, s, c);
-        kerr_accel_half<double>(M, a, r, s * s, s * c, ut, ur, uth, uph, at2, ar, ath, aph2);
+        if (ZERO_A)
+            schwarzschild_accel_half<double>(M, r, s * s, s * c, ut, ur, uth, uph, at2, ar, ath, aph2);
+        else
+            kerr_accel_half<double>(M, a, r, s * s, s * c, ut, ur, uth, uph, at2, ar, ath, aph2);
     }
 };
 
 // One FP64 RK4 step (Christoffel form).  SHORT = true for the fixed-step integrators
 // (small stage offsets), false for steps whose stage points move further (the camera's
-// h = h0 max(1, r / h_r0)).  Tab: where the trigonometry table is read from.
-template <bool SHORT = true, typename Tab = TabGlobal>
+// h = h0 max(1, r / h_r0)).  Tab: where the trigonometry table is read from.  ZERO_A: S.a = 0.
+template <bool SHORT = true, typename Tab = TabGlobal, bool ZERO_A = false>
 __device__ __forceinline__ void rk4_step_f64(const Spacetime &S, double h, const double y[8],
                                              double y1[8], double sr[3])
 {
-    AccelHalfF64T<StageTrigT<SHORT, Tab>> f{S.M, S.a, {}};
+    AccelHalfF64T<StageTrigT<SHORT, Tab>, ZERO_A> f{S.M, S.a, {}};
     rk4_step_half(f, h, y, y1, sr);
 }
 
@@ -271,8 +274,8 @@ __device__ __forceinline__ void rk4_step_f64_zone(const Spacetime &S, double h, 
 
 // FP64 canonical right-hand side (Hamiltonian form) as a functor for rk4_ham_step.  S2: the
 // form of the FP64 kernels (kerr_ham_s2), else the one that the FP32 stages of the
-// compensated integrator evaluate (kerr_ham).
-template <typename Trig, bool S2 = true>
+// compensated integrator evaluate (kerr_ham).  ZERO_A: a = 0 (with S2).
+template <typename Trig, bool S2 = true, bool ZERO_A = false>
 struct HamF64T {
     double M, a;
     const HamConst<double> &P;
@@ -283,18 +286,21 @@ struct HamF64T {
     {
         double s, c;
         trig(stage, th, s, c);
-        if (S2)
+        if (ZERO_A)
+            schwarzschild_ham_s2<double>(M, r, s * s, s * c, pr, pth, P, dt, dr, dth, dph, dpr, dpth);
+        else if (S2)
             kerr_ham_s2<double>(M, a, r, s * s, s * c, pr, pth, P, dt, dr, dth, dph, dpr, dpth);
         else
             kerr_ham<double>(M, a, r, s, c, pr, pth, P, dt, dr, dth, dph, dpr, dpth);
     }
 };
 
+template <bool ZERO_A = false>
 __device__ __forceinline__ void rk4_step_ham_f64(const Spacetime &S, const HamConst<double> &P,
                                                  double h, const double z[8], double z1[8],
                                                  double sr[3])
 {
-    HamF64T<StageTrigT<true>> f{S.M, S.a, P, {}};
+    HamF64T<StageTrigT<true>, true, ZERO_A> f{S.M, S.a, P, {}};
     rk4_ham_step(f, h, z, z1, sr);
 }
 

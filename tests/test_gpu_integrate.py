@@ -426,3 +426,32 @@ def test_stop_rules_next_to_their_limits(m, orc, form):
     for j, want in enumerate((2, 1, 4, 4)):  # the lanes meet their limits
         assert (ref[1][j * n:(j + 1) * n] == want).sum() >= n // 3, (j, ref[1][j * n:(j + 1) * n])
     assert (ref[1][4 * n:] == 0).all()
+
+
+@pytest.mark.parametrize("formulation", ["christoffel", "hamiltonian"])
+def test_schwarzschild_kernel_is_the_general_one(m, orc, formulation):
+    """A uniform launch at a = 0 takes the kernel without the terms that are then zero (M = 1
+    and other masses); its bits equal those of the general kernel, which a mixed batch runs:
+    bound and plunging orbits, lanes next to the poles and lanes that are not finite."""
+    import torch
+    sts = [(1.0, 0.0), (2.0, 0.0), (0.5, 0.0)]
+    n = 1500
+    idx = (np.arange(n) % 3).astype(np.int32)
+    rc, s0, _, _ = orc.ic_constants(12, sts, n, KERR_RANGES, st_of_lane=idx)
+    s0 = np.ascontiguousarray(s0)
+    rng = np.random.default_rng(3)
+    s0[2, :90] = np.concatenate([10.0 ** rng.uniform(-5.0, -1.0, 45),
+                                 math.pi - 10.0 ** rng.uniform(-5.0, -1.0, 45)])
+    s0[5, 90:200] = -rng.uniform(0.5, 20.0, 110)
+    for j, v in enumerate((math.nan, math.inf, -math.inf, 1e300, -1e300, 1e160, 0.0)):
+        for c in range(8):
+            s0[c, 200 + 24 * j + 3 * c:200 + 24 * j + 3 * c + 3] = v
+    kw = dict(formulation=formulation)
+    mixed = run_gpu(m, sts, s0, 0.02, 500, st_of_lane=to_dev(idx, torch.int32), **kw)
+    assert set(np.unique(mixed[1])) >= {0, 1, 4}
+    for k, stk in enumerate(sts):
+        sel = idx == k
+        one = run_gpu(m, [stk], s0[:, sel], 0.02, 500, **kw)
+        np.testing.assert_array_equal(one[0], mixed[0][:, sel])
+        np.testing.assert_array_equal(one[1], mixed[1][sel])
+        np.testing.assert_array_equal(one[2], mixed[2][sel])
