@@ -3,16 +3,22 @@
 // Forward: malbec_integrate with checkpoint_every = K stores the state every K steps.
 // Backward, per lane and per segment s = last .. 0: recompute the K step-start
 // states from checkpoint s into the workspace (coalesced [K][8][n] doubles), then
-// walk them in reverse applying the transposed RK4 step (rk4_vjp):
+// walk them in reverse applying the transposed RK4 step (rk4_vjp_half):
 //     lam_y  = lam + J(Y4)^T lam_k4 + J(Y3)^T lam_k3 + J(Y2)^T lam_k2 + J(y)^T lam_k1,
 //     lam_k4 = h/6 lam, lam_k3 = h/3 lam + h J(Y4)^T lam_k4,
 //     lam_k2 = h/3 lam + h/2 J(Y3)^T lam_k3, lam_k1 = h/6 lam + h/2 J(Y2)^T lam_k2,
 // where J = df/dy.  f = (u, a(r, theta, u)); the transposed Jacobian of the
 // acceleration is the hand-written reverse mode of the regrouped acceleration the
-// forward kernels evaluate (kerr_accel_vjp), at the stage points the forward step
+// forward kernels evaluate (kerr_accel_half_vjp), at the stage points the forward step
 // forms.  Steps a lane did not take (after it stopped, or a terminal step whose result
 // was discarded) are the identity.  The next state of the reverse walk is loaded
 // while the current one is transposed.
+//
+// What bounds it: FP64 VALU issue at one wave per SIMD (0.86 of the CU-busy time; 358 vector
+// registers), 363 vector instructions per step recomputed and about 950 per step transposed.
+// A training step of 65,536 lanes x 1,024 steps (forward, backward) with the transposed
+// Jacobian of kerr_accel 5.36 ms, with that of kerr_accel_half 5.02; 20,000 lanes x 512 steps
+// 2.46 and 2.30 (one MI355X, the same machine before and after).
 #include "dual.hpp"
 #include "internal.hpp"
 
@@ -37,32 +43,36 @@ struct AdjArgs {
 
 // The acceleration of the forward kernels (the same stage trigonometry: a fresh sin
 // and cos at the step's start, short rotations at the later stages) with its
-// transposed Jacobian for rk4_vjp.  The stage points and the sin and cos of each (the
+// transposed Jacobian for rk4_vjp_half.  The stage points and the sin and cos of each (the
 // last stage's formed by prepare) are kept from the forward pass, so the reverse pass
 // evaluates no trigonometry.  (Keeping them in LDS instead of registers, to lower the
 // register count, measured 4 % slower at the one wave per SIMD that 65,536 lanes give.)
 struct AdjAccel {
     double M, a;
     StageTrigT<true, TabLds> trig;
-    double Ys[4][6], sk[4], ck[4];
+    double Ys[4][6], s2[4], sc[4];  // s2 = sin^2 theta, sc = sin theta cos theta
     __device__ __forceinline__ double &Y(int st, int k) { return Ys[st][k]; }
     __device__ __forceinline__ void keep() {}
-    __device__ __forceinline__ void operator()(int stage, double r, double th, double ut, double ur,
-                                               double uth, double uph, double &at, double &ar,
-                                               double &ath, double &aph)
+    __device__ __forceinline__ void prepare(int stage, double th)
     {
-        trig(stage, th, sk[stage], ck[stage]);
-        kerr_accel<double>(M, a, r, sk[stage], ck[stage], ut, ur, uth, uph, at, ar, ath, aph);
+        double s, c;
+        trig(stage, th, s, c);
+        s2[stage] = s * s;
+        sc[stage] = s * c;
     }
-    __device__ __forceinline__ void prepare(int stage, double th) { trig(stage, th, sk[stage], ck[stage]); }
+    __device__ __forceinline__ void operator()(int stage, double r, double th, double ut, double ur,
+                                               double uth, double uph, double &at2, double &ar,
+                                               double &ath, double &aph2)
+    {
+        prepare(stage, th);
+        kerr_accel_half<double>(M, a, r, s2[stage], sc[stage], ut, ur, uth, uph, at2, ar, ath, aph2);
+    }
     __device__ __forceinline__ void vjp(int stage, double r, double, double ut, double ur, double uth,
-                                        double uph, double bat, double bar, double bath, double baph,
+                                        double uph, double bat2, double bar, double bath, double baph2,
                                         double &rb, double &thb, double ub[4])
     {
-        const double s = sk[stage], c = ck[stage];
-        double sb, cb;
-        kerr_accel_vjp<double>(M, a, r, s, c, ut, ur, uth, uph, bat, bar, bath, baph, rb, sb, cb, ub);
-        thb = fma(sb, c, -cb * s);  // d/dtheta through s = sin theta, c = cos theta
+        kerr_accel_half_vjp<double>(M, a, r, s2[stage], sc[stage], ut, ur, uth, uph, bat2, bar, bath,
+                                    baph2, rb, thb, ub);
     }
 };
 
@@ -131,7 +141,7 @@ __global__ void __launch_bounds__(256) adjoint_kernel(AdjArgs A, StTable T)
             }
             if (accepted) {
                 AdjAccel f{S.M, S.a, {}, {}, {}, {}};
-                rk4_vjp(f, A.h, y, lam);
+                rk4_vjp_half(f, A.h, y, lam);
             }
         }
     }

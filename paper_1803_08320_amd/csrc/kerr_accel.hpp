@@ -308,7 +308,8 @@ MALBEC_HD inline void schwarzschild_accel_half(T M, T r, T s2, T sc, T ut, T ur,
     ath = fma(-sig2, uth, sc * fma(DI, uu, q * uu));
 }
 
-// Reverse mode of kerr_accel: given the cotangents (bat, bar, bath, baph) of
+// Reverse mode of kerr_accel, against which the host checks hold that of kerr_accel_half (which
+// the adjoint kernel runs): given the cotangents (bat, bar, bath, baph) of
 // (a^t, a^r, a^theta, a^phi), the cotangents of r, s = sin theta, c = cos theta and
 // of the 4-velocity (ub[0..3] for u^t, u^r, u^theta, u^phi), i.e. the transposed
 // Jacobian of the computed expression applied to b.  The forward expressions are
@@ -504,6 +505,109 @@ MALBEC_HD inline void kerr_accel_vjp(T M, T a, T r, T s, T c, T ut, T ur, T uth,
     ub[3] = uphb;
 }
 
+// Transposed Jacobian of kerr_accel_half (in r, theta and u; s2' = 2 sc, sc' = 1 - 2 s2 and
+// cot' = -1/s2 in theta): bt, br, bh, bp are the cotangents of a^t / 2, a^r, a^theta and
+// a^phi / 2; rb, thb and ub[4] receive those of r, theta and u.  With them the four results
+// are one scalar S, which the forward pass groups by what its terms share,
+//   S = (u^r / Delta) Z + n N + m (u^phi)^2 + br DI V HV + br u^r (r - M) u^r / Delta
+//       - 2 sigma (br u^r + bh u^theta) + bh s c q zeta^2 + u^theta (c3 q B - bp cot u^phi),
+// so that a cotangent of each shared quantity is formed once, and 1/rho^2, 1/Delta and
+// cot theta are differentiated themselves instead of through the reciprocal that they are
+// computed from.  About 152 instructions where kerr_accel_vjp takes 180.
+template <typename T>
+MALBEC_HD inline void kerr_accel_half_vjp(T M, T a, T r, T s2, T sc, T ut, T ur, T uth, T uph, T bt,
+                                          T br, T bh, T bp, T &rb, T &thb, T ub[4])
+{
+    // the forward quantities of kerr_accel_half
+    const T a2 = a * a;
+    const T A = fma(r, r, a2);
+    const T rho2 = fma(-a2, s2, A);
+    const T M2 = M + M;
+    const T Delta = fma(-M2, r, A);
+    const T Ds2 = Delta * s2;
+    const T inv = recip(rho2 * Ds2);
+    const T irho2 = inv * Ds2;
+    const T iDs2 = inv * rho2;
+    const T iDelta = iDs2 * s2;
+    const T is2 = iDs2 * Delta;             // 1 / s^2
+    const T cot = is2 * sc;
+    const T DI = Delta * irho2;
+    const T ri = r * irho2;
+    const T q = M2 * ri;
+    const T q_r = fma(-q, ri, M * irho2);
+    const T air = a * irho2;
+    const T asc = a * sc;
+    const T k1 = asc * air;
+    const T as2 = a * s2;
+    const T V = fma(-as2, uph, ut);
+    const T B = air * V;
+    const T zeta = uph - B;
+    const T qB = q * B;
+    const T HV = q_r * V;
+    const T ru = r * uph;
+    const T qru = q * ru;
+    const T urD = ur * iDelta;
+    const T sigma = fma(ri, ur, -(k1 * uth));
+    const T sig2 = sigma + sigma;
+    const T e = ur * urD;
+    const T N = fma(uth, uth, e);
+    const T uu = uph * uph;
+    const T G = fma(s2, uu, N);
+    const T rM = r - M;
+
+    // coefficients of S
+    const T c1 = fma(bt, A, bp * a);        // of (u^r / Delta) HV
+    const T c2 = fma(bt, as2, bp);          // of (u^r / Delta) q r u^phi
+    const T c3 = fma(bt, asc, bp * cot);    // of u^theta q B
+    const T Z = fma(c1, HV, fma(c2, qru, -(bp * ru)));
+    const T W = fma(br, ur, bh * uth);
+    const T bD = br * DI;
+    const T bDr = bD * r;
+    const T n = fma(-bh, k1, bDr);
+    const T bhsc = bh * sc;
+    const T m = fma(bhsc, DI, bDr * s2);
+    const T nb = fma(br, rM, n);
+
+    // cotangents of the velocity products, then of u
+    const T urDb = fma(ur, nb, Z);
+    const T HVb = fma(bD, V, c1 * urD);
+    const T qrub = c2 * urD;
+    const T rub = fma(q, qrub, -(bp * urD));
+    const T qBb = c3 * uth;
+    const T bz = bhsc * zeta;
+    const T bqz = q * bz;
+    const T zetab = bqz + bqz;
+    const T Bb = fma(q, qBb, -zetab);
+    const T Vb = fma(bD, HV, fma(q_r, HVb, air * Bb));
+    const T bpc = bp * cot;
+    const T sigb = -(W + W);
+    ub[0] = Vb;
+    ub[1] = fma(iDelta, urDb, fma(nb, urD, fma(ri, sigb, -(sig2 * br))));
+    ub[2] = fma(c3, qB, fma(-bpc, uph, fma(n + n, uth, fma(-k1, sigb, -(sig2 * bh)))));
+    ub[3] = fma(m + m, uph, fma(-bpc, uth, fma(r, rub, fma(-as2, Vb, zetab))));
+
+    // cotangents of the coefficients of r and theta
+    const T t1 = bt * urD;
+    const T q_rb = HVb * V;
+    const T qb = fma(-ri, q_rb, fma(qrub, ru, fma(qBb, B, bz * zeta)));
+    const T k1b = -fma(uth, sigb, bh * N);
+    const T airb = fma(k1b, asc, Bb * V);
+    const T ascb = fma(k1b, air, (bt * uth) * qB);
+    const T as2b = fma(-uph, Vb, t1 * qru);
+    const T cotb = (bp * uth) * (qB - uph);
+    const T iDeltab = urDb * ur;
+    const T DIb = fma(br, fma(V, HV, r * G), bhsc * uu);
+    const T rib = fma(M2, qb, fma(-q, q_rb, ur * sigb));
+    const T irho2b = fma(DIb, Delta, fma(a, airb, fma(rib, r, M * q_rb)));
+    const T rho2b = -(irho2b * (irho2 * irho2));
+    const T Deltab = fma(-iDeltab, iDelta * iDelta, DIb * irho2);
+    const T Ab = fma(t1, HV, rho2b + Deltab);
+    const T scb = fma(a, ascb, bh * fma(DI, uu, q * (zeta * zeta)));
+    const T s2b = fma(-a2, rho2b, fma(a, as2b, bDr * uu));
+    rb = fma(r + r, Ab, fma(-M2, Deltab, fma(rib, irho2, fma(br, e, fma(bD, G, uph * rub)))));
+    thb = fma(-is2, cotb, fma(sc + sc, s2b, fma(T(-2), s2, T(1)) * scb));
+}
+
 // The direct form: coefficients, then contraction, as the adjoint differentiates it.
 template <typename T>
 MALBEC_HD inline void kerr_accel_direct(T M, T a, T r, T s, T c, T ut, T ur, T uth, T uph, T &at,
@@ -631,7 +735,8 @@ MALBEC_HD inline void rk4_delta(Accel &accel, T h, const T y[8], T d[8], T sr[3]
     for (int k = 0; k < 8; ++k) d[k] = h6 * acc[k];
 }
 
-// Transposed RK4 step: lam <- (d y1 / d y)^T lam for the step y -> y1 of rk4_step.
+// Transposed RK4 step: lam <- (d y1 / d y)^T lam for the step y -> y1 of rk4_step (the host's
+// check of rk4_vjp_half below).
 // With k_i = f(Y_i), Y_1 = y, Y_2 = y + h/2 k_1, Y_3 = y + h/2 k_2, Y_4 = y + h k_3 and
 // y1 = y + h/6 (k_1 + 2 k_2 + 2 k_3 + k_4), the cotangents of the stage values are
 //   lk_4 = h/6 lam,  lk_3 = h/3 lam + h J_4^T lk_4,
@@ -698,6 +803,65 @@ MALBEC_HD inline void rk4_vjp(F &f, T h, const T y[8], T lam[8])
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) lam[k] = ly[k];
+}
+
+// The same for the step of rk4_step_half: F's operator() returns a^t / 2, a^r, a^theta, a^phi / 2,
+// and vjp takes the cotangents of those (twice lk of u^t and u^phi).
+template <typename T, typename F>
+MALBEC_HD inline void rk4_vjp_half(F &f, T h, const T y[8], T lam[8])
+{
+    const T hh = T(0.5) * h, h2 = h + h;
+    {
+        T at2, ar, ath, aph2;
+        T r = y[1], th = y[2], ut = y[4], ur = y[5], uth = y[6], uph = y[7];
+        f.Y(0, 0) = r; f.Y(0, 1) = th; f.Y(0, 2) = ut; f.Y(0, 3) = ur; f.Y(0, 4) = uth; f.Y(0, 5) = uph;
+        f(0, r, th, ut, ur, uth, uph, at2, ar, ath, aph2);
+        r = fma(hh, y[5], y[1]); th = fma(hh, y[6], y[2]);
+        ut = fma(h, at2, y[4]); ur = fma(hh, ar, y[5]); uth = fma(hh, ath, y[6]); uph = fma(h, aph2, y[7]);
+        f.Y(1, 0) = r; f.Y(1, 1) = th; f.Y(1, 2) = ut; f.Y(1, 3) = ur; f.Y(1, 4) = uth; f.Y(1, 5) = uph;
+        f(1, r, th, ut, ur, uth, uph, at2, ar, ath, aph2);
+        r = fma(hh, ur, y[1]); th = fma(hh, uth, y[2]);
+        ut = fma(h, at2, y[4]); ur = fma(hh, ar, y[5]); uth = fma(hh, ath, y[6]); uph = fma(h, aph2, y[7]);
+        f.Y(2, 0) = r; f.Y(2, 1) = th; f.Y(2, 2) = ut; f.Y(2, 3) = ur; f.Y(2, 4) = uth; f.Y(2, 5) = uph;
+        f(2, r, th, ut, ur, uth, uph, at2, ar, ath, aph2);
+        r = fma(h, ur, y[1]); th = fma(h, uth, y[2]);
+        ut = fma(h2, at2, y[4]); ur = fma(h, ar, y[5]); uth = fma(h, ath, y[6]); uph = fma(h2, aph2, y[7]);
+        f.Y(3, 0) = r; f.Y(3, 1) = th; f.Y(3, 2) = ut; f.Y(3, 3) = ur; f.Y(3, 4) = uth; f.Y(3, 5) = uph;
+        f.prepare(3, th);
+    }
+    f.keep();
+
+    // g = h/3 lam, with that of u^t and u^phi doubled; lk the cotangents of the stage values
+    // (x, then a^t / 2, a^r, a^theta, a^phi / 2)
+    const T h3 = h * T(1.0 / 3.0), h23 = h3 + h3;
+    T g[8], lk[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) { g[k] = (k == 4 || k == 7 ? h23 : h3) * lam[k]; lk[k] = T(0.5) * g[k]; }
+#pragma unroll
+    for (int st = 3; st >= 0; --st) {
+        // mu = J(Y_st)^T lk
+        T mr, mth, mu[4];
+        f.vjp(st, f.Y(st, 0), f.Y(st, 1), f.Y(st, 2), f.Y(st, 3), f.Y(st, 4), f.Y(st, 5), lk[4],
+              lk[5], lk[6], lk[7], mr, mth, mu);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) mu[k] += lk[k];
+        lam[1] += mr;
+        lam[2] += mth;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) lam[4 + k] += mu[k];
+        if (st > 0) {
+            // lk of the previous stage: its weight times lam plus its offset coefficient times mu
+            const T o = st == 3 ? h : hh, o2 = o + o;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) lk[k] = st == 1 ? T(0.5) * g[k] : g[k];
+            lk[1] = fma(o, mr, lk[1]);
+            lk[2] = fma(o, mth, lk[2]);
+            lk[4] = fma(o2, mu[0], lk[4]);
+            lk[5] = fma(o, mu[1], lk[5]);
+            lk[6] = fma(o, mu[2], lk[6]);
+            lk[7] = fma(o2, mu[3], lk[7]);
+        }
+    }
 }
 
 }  // namespace malbec
