@@ -197,7 +197,9 @@ def _check(rc):
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream's handle.  Asked of torch as a number: current_stream() builds a
+    Stream object first (2.6 us of a call's 10 us on the host; this is 0.25 us)."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t: Optional[torch.Tensor], dtype=None, numel=None, name="tensor"):
@@ -222,7 +224,7 @@ class _Batch:
         if not 1 <= len(sts) <= MAX_SPACETIMES:
             raise ValueError("need 1..%d spacetimes" % MAX_SPACETIMES)
         self.arr = (c_spacetime * len(sts))(*[c_spacetime(M, a) for M, a in sts])
-        self.c = c_batch(C.cast(self.arr, C.POINTER(c_spacetime)), len(sts), 0,
+        self.c = c_batch(self.arr, len(sts), 0,
                          _ptr(st_of_lane, torch.int32, n, "st_of_lane"))
 
 
@@ -294,17 +296,17 @@ def integrate(state: torch.Tensor, status: torch.Tensor, steps: torch.Tensor, sp
     n = state.shape[-1]
     prec = {"f64": F64, "f32k": F32_KAHAN}[precision]
     form = {"christoffel": FORM_CHRISTOFFEL, "hamiltonian": FORM_HAMILTONIAN}[formulation]
+    sts = _spacetimes(spacetimes)
     if block == 0 and checkpoint_every == 0 and state.is_cuda:
         from . import autotune
-        shape = autotune.lookup_integrate(n, len(_spacetimes(spacetimes)), precision, formulation,
-                                          persistent)
+        shape = autotune.lookup_integrate(n, len(sts), precision, formulation, persistent)
         if shape:
             block = shape[0]
             if persistent and steps_per_chunk == 0:
                 steps_per_chunk = shape[1]
     run = c_run(h, n_steps, prec, block, horizon_factor, r_escape, fp64_zone_factor,
                 steps_per_chunk, checkpoint_every, int(persistent), form)
-    b = _Batch(_spacetimes(spacetimes), st_of_lane, n)
+    b = _Batch(sts, st_of_lane, n)
     if checkpoint_every > 0:
         if checkpoints is None:
             raise ValueError("checkpoint_every > 0 needs a checkpoints tensor")

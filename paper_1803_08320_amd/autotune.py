@@ -29,18 +29,22 @@ _mem = None  # the cache file's content, loaded once per process
 _arch = {}
 
 
+_default_path = os.path.join(_HERE, "_build", "autotune.json")
+
+
 def _cache_path():
-    return os.environ.get("MALBEC_TUNE_CACHE", os.path.join(_HERE, "_build", "autotune.json"))
+    return os.environ.get("MALBEC_TUNE_CACHE", _default_path)
 
 
 def _load():
     global _mem
-    if _mem is None or _mem[0] != _cache_path():
+    path = _cache_path()
+    if _mem is None or _mem[0] != path:
         try:
-            with open(_cache_path()) as f:
-                _mem = (_cache_path(), json.load(f))
+            with open(path) as f:
+                _mem = (path, json.load(f))
         except (OSError, ValueError):
-            _mem = (_cache_path(), {})
+            _mem = (path, {})
     return _mem[1]
 
 
@@ -88,7 +92,10 @@ def _integrate_key(n, n_st, precision, formulation, persistent):
 def lookup_integrate(n, n_st, precision="f64", formulation="christoffel", persistent=False):
     """The cached (block, steps_per_chunk) of an integrate launch, or None (no timing)."""
     with _lock:
-        e = _load().get(_integrate_key(n, n_st, precision, formulation, persistent))
+        cache = _load()
+        if not cache:  # nothing tuned: no key to build
+            return None
+        e = cache.get(_integrate_key(n, n_st, precision, formulation, persistent))
     return (e["block"], e["chunk"]) if e else None
 
 
