@@ -41,7 +41,7 @@ PEAK_FP32_VECTOR_TFLOPS = 157.3
 # figures hold for the sources that define the kernel's body, whose SHA-256 is given;
 # after any change to them the traffic is reported as null until the counters are
 # taken again.
-KERNEL_SOURCES = ("integrate.hip", "kerr_device.hpp", "kerr_accel.hpp", "ham_accel.hpp",
+KERNEL_SOURCES = ("integrate.hip", "f64_prog.hpp", "kerr_device.hpp", "kerr_accel.hpp", "ham_accel.hpp",
                   "persistent.hpp", "sincos_table.hpp")
 TRAFFIC = {"sources_sha256": "5a6ab0341c68de51e9c473087ee15a8d581b8cf3b3e74fcb06994aca22ca6b95",
            "fetch_kib": 36960.0625, "fetch_scale": 1048576 / 524307.5625,

@@ -84,15 +84,8 @@ struct AdProg {
     // stored: kept in scalar registers across the attempts, they pushed the controls and the
     // tableau's constants out into vector lanes (113 v_readlane in the kernel, most of them in
     // the attempt; 36 now: to tau = 400 at a tolerance of 1e-12, 65,536 lanes 4.53 -> 4.34 ms,
-    // 262,144 lanes 5.21 -> 5.06, 1,048,576 lanes 13.94 -> 13.83).  AdArgs is the kernels' first
-    // argument.
+    // 262,144 lanes 5.21 -> 5.06, 1,048,576 lanes 13.94 -> 13.83).
     typedef const __attribute__((address_space(4))) AdArgs *Args;
-    __device__ static __forceinline__ Args args()
-    {
-        Args p = (Args)__builtin_amdgcn_kernarg_segment_ptr();
-        asm volatile("" : "+s"(p));
-        return p;
-    }
     __device__ static __forceinline__ int64_t lane_of(Args A, int64_t item)
     {
         const uint32_t *order = A->order;
@@ -100,7 +93,7 @@ struct AdProg {
     }
     __device__ __forceinline__ bool load(int64_t item, Lane &L)
     {
-        const Args A = args();
+        const Args A = first_arg<AdArgs>();
         const int64_t i = lane_of(A, item);
         L.st = A->status[i];
         if (L.st != kActive) return false;
@@ -192,7 +185,7 @@ struct AdProg {
     {
         // the index is laundered so that the addresses of the loads are not kept
         // live across the attempts for reuse here
-        const Args A = args();
+        const Args A = first_arg<AdArgs>();
         const int64_t i = lane_of(A, opaque(item));
 #pragma unroll
         for (int k = 0; k < 8; ++k) A->state[k * A->n + i] = L.y[k];

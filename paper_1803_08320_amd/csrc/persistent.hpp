@@ -13,6 +13,17 @@
 
 namespace malbec {
 
+// The kernel's first argument, of type A, read again from the kernel's arguments: a Prog takes
+// its arrays' addresses from there where a lane is loaded or stored.  Kept in scalar registers
+// across the steps, they push what the steps use out into vector lanes.
+template <typename A>
+__device__ __forceinline__ const __attribute__((address_space(4))) A *first_arg()
+{
+    auto p = (const __attribute__((address_space(4))) A *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
 // Prog provides:  typename Prog::Lane;
 //   bool load(int64_t item, Lane&)   -- false: nothing to do for this item
 //   bool step(Lane&)                 -- one step; true when the item is finished
