@@ -21,16 +21,16 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=on", "--offload-arch=" + 
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-fvisibility=hidden", "-Wall", "-Wno-unused-function", "-Wno-unused-command-line-argument"]
 
-# These kernels are chains of dependent FP64 arithmetic at one to four waves per SIMD: scheduled
+# These kernels are chains of dependent arithmetic at one to four waves per SIMD: scheduled
 # for instruction-level parallelism rather than for occupancy, and not reordered again after
 # register allocation.  On one MI355X against the default (the same results): 1,024 Kerr lanes
 # x 1,000 steps 0.867 -> 0.850 ms, in the Hamiltonian form 0.739 -> 0.707, 262,144 lanes 3.02 ->
 # 2.99 and 2.42 -> 2.39 ms, 20,000 monitored lanes 0.920 -> 0.896 ms, the gridded kernel (262,144
-# lanes x 400 steps) 6.42 -> 6.10 ms, a 512 x 512 camera image 3.14 -> 3.03 ms.  The adaptive
-# and the FP32-compensated kernels are slower with it (262,144 lanes 4.95 -> 5.14 ms; the
-# monitored Hamiltonian form 1.47 -> 1.77 ms), and it changes nothing for the adjoint.
+# lanes x 400 steps) 6.42 -> 6.10 ms, a 512 x 512 camera image 3.14 -> 3.03 ms, 262,144
+# FP32-compensated lanes x 600 steps 1.33 -> 1.25 ms.  The adaptive kernel is slower with it
+# (262,144 lanes 4.95 -> 5.14 ms), and it changes nothing for the adjoint.
 SCHEDULE = ["-mllvm", "-amdgpu-sched-strategy=max-ilp", "-mllvm", "-enable-post-misched=0"]
-SCHEDULED = ("camera.hip", "grid.hip", "integrate.hip", "trajectory.hip")
+SCHEDULED = ("camera.hip", "grid.hip", "integrate.hip", "mixed.hip", "trajectory.hip")
 
 
 def hipcc() -> str:

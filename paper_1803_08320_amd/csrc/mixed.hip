@@ -145,10 +145,12 @@ __device__ __forceinline__ void two_sum(float a, float b, float &s, float &e)
 //   Hamiltonian form    20,000 lanes 0.562 -> 0.525 ms, 262,144 lanes 1.19 -> 1.12 ms; persistent, 16
 //                       spacetimes: 262,144 lanes 1.45 -> 1.30 ms, 1,048,576 lanes 4.49 -> 4.28 ms
 //   Christoffel form    20,000 lanes 0.629 -> 0.591 ms, 262,144 lanes 1.355 -> 1.328 ms
+// and, with the schedule for instruction parallelism (_build_lib.py), to 0.48, 1.07, 1.25, 4.1 and
+// 0.55, 1.25 ms.
 // The persistent kernel of the Christoffel form goes step by step: held to the 128 registers of
 // four waves per SIMD, it is slower in pairs (393,216 lanes 2.07 ms by steps, 2.31 in pairs;
 // 262,144 lanes 1.49 and 1.52).
-template <bool HAM>
+template <bool HAM, bool QUEUE>
 struct MixProg {
     const MixArgs &A;
     const Spacetime *table;
@@ -163,15 +165,24 @@ struct MixProg {
         HamConst<float> P32;
         int32_t st, taken;
     };
+    // read again from the kernel's arguments in the persistent kernels (QUEUE)
+    __device__ __forceinline__ auto args() const
+    {
+        if constexpr (QUEUE)
+            return first_arg<MixArgs>();
+        else
+            return &A;
+    }
     __device__ __forceinline__ bool load(int64_t i, Lane &L)
     {
-        L.st = A.status[i];
+        const auto *A = args();
+        L.st = A->status[i];
         if (L.st != kActive) return false;
         int32_t sid = 0;
         if (multi) {
-            sid = A.st_of_lane[i];
+            sid = A->st_of_lane[i];
             if (sid < 0 || sid >= n_st) {
-                A.status[i] = kNonfinite;
+                A->status[i] = kNonfinite;
                 return false;
             }
         }
@@ -180,13 +191,13 @@ struct MixProg {
         if ((double)L.rs32 > L.S.r_stop) L.rs32 = __int_as_float(__float_as_int(L.rs32) - 1);
         L.r_safe = safe_above(fmax(L.S.r_stop, L.S.r_zone));
 #pragma unroll
-        for (int k = 0; k < 8; ++k) split(A.state[k * A.n + i], L.hi[k], L.lo[k]);
+        for (int k = 0; k < 8; ++k) split(A->state[k * A->n + i], L.hi[k], L.lo[k]);
         if (HAM) {
             L.P64 = ham_const(L.S.a, (double)L.hi[4] + (double)L.lo[4], (double)L.hi[7] + (double)L.lo[7]);
             L.P32 = ham_const((float)L.S.a, L.hi[4], L.hi[7]);
         }
         L.taken = 0;
-        return A.n_steps > 0;
+        return A->n_steps > 0;
     }
     // The FP32 stages on hi: the increment d and the stage radii.
     __device__ __forceinline__ void fp32_delta(const Lane &L, const float hi[8], float d[8],
@@ -302,11 +313,12 @@ struct MixProg {
     }
     __device__ __forceinline__ void store(int64_t item, const Lane &L)
     {
+        const auto *A = args();
         const int64_t i = opaque(item);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) A.state[k * A.n + i] = (double)L.hi[k] + (double)L.lo[k];
-        A.status[i] = L.st;
-        A.steps[i] += L.taken;
+        for (int k = 0; k < 8; ++k) A->state[k * A->n + i] = (double)L.hi[k] + (double)L.lo[k];
+        A->status[i] = L.st;
+        A->steps[i] += L.taken;
     }
     __device__ static __forceinline__ void state64(const Lane &L, double y[8])
     {
@@ -317,7 +329,7 @@ struct MixProg {
 
 // The Christoffel-form kernels are held to 128 registers, four waves per SIMD (the
 // FP64 zone step sets the peak; the FP32 step alone needs about 80); the Hamiltonian
-// form's zone step needs about 150 and keeps the compiler's default (three waves).
+// form's zone step needs about 160 and keeps the compiler's default (three waves).
 template <bool MULTI, bool HAM>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HAM ? 1 : 4, HAM ? 8 : 4)))
 rk4_f32k_kernel(MixArgs A, StTable T)
@@ -327,8 +339,8 @@ rk4_f32k_kernel(MixArgs A, StTable T)
     __syncthreads();
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= A.n) return;
-    MixProg<HAM> P{A, lds_st, MULTI, T.n_st};
-    typename MixProg<HAM>::Lane L;
+    MixProg<HAM, false> P{A, lds_st, MULTI, T.n_st};
+    typename MixProg<HAM, false>::Lane L;
     if (!P.load(i, L)) return;
     P.run(L, A.n_steps);
     P.store(i, L);
@@ -341,7 +353,7 @@ rk4_f32k_persistent_kernel(MixArgs A, StTable T, unsigned long long *counter, in
     __shared__ Spacetime lds_st[kMaxSt];
     for (int k = threadIdx.x; k < T.n_st; k += blockDim.x) lds_st[k] = T.st[k];
     __syncthreads();
-    MixProg<HAM> P{A, lds_st, MULTI, T.n_st};
+    MixProg<HAM, true> P{A, lds_st, MULTI, T.n_st};
     persistent_loop<HAM>(P, A.n, counter, chunk);
 }
 
@@ -356,25 +368,28 @@ __global__ void __launch_bounds__(256) rk4_f32k_monitor_kernel(MixArgs A, StTabl
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= A.n) return;
     __shared__ double lds_mon[8 * kMonLanes];
-    MonProg<MixProg<HAM>, HAM> P{MixProg<HAM>{A, lds_st, multi != 0, T.n_st}, MA, &lds_mon[threadIdx.x]};
-    typename MonProg<MixProg<HAM>, HAM>::Lane L;
+    typedef MixProg<HAM, false> Prog;
+    MonProg<Prog, HAM> P{Prog{A, lds_st, multi != 0, T.n_st}, MA, &lds_mon[threadIdx.x]};
+    typename MonProg<Prog, HAM>::Lane L;
     if (!P.load(i, L)) return;
     while (!P.step(L)) {
     }
     P.store(i, L);
 }
 
+// Unless held to three waves per SIMD the Hamiltonian form takes 177 registers, which leaves two
+// (262,144 lanes of 16 spacetimes 1.54 ms, with three 1.43).
 template <bool HAM>
-__global__ void __launch_bounds__(256) rk4_f32k_monitor_persistent_kernel(MixArgs A, StTable T,
-                                                                          MonArgs MA, int32_t multi,
-                                                                          unsigned long long *counter,
-                                                                          int32_t chunk)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HAM ? 3 : 1, 8)))
+rk4_f32k_monitor_persistent_kernel(MixArgs A, StTable T, MonArgs MA, int32_t multi,
+                                   unsigned long long *counter, int32_t chunk)
 {
     __shared__ Spacetime lds_st[kMaxSt];
     for (int k = threadIdx.x; k < T.n_st; k += blockDim.x) lds_st[k] = T.st[k];
     __syncthreads();
     __shared__ double lds_mon[8 * kMonLanes];
-    MonProg<MixProg<HAM>, HAM> P{MixProg<HAM>{A, lds_st, multi != 0, T.n_st}, MA, &lds_mon[threadIdx.x]};
+    typedef MixProg<HAM, true> Prog;
+    MonProg<Prog, HAM> P{Prog{A, lds_st, multi != 0, T.n_st}, MA, &lds_mon[threadIdx.x]};
     persistent_loop(P, A.n, counter, chunk);
 }
 
