@@ -108,6 +108,65 @@ __global__ void __launch_bounds__(256) rk4_f64_kernel(IntArgs A, StTable T)
     }
 }
 
+// A number of lanes that fills the chip unevenly, for instance 100,003: 1,563 wavefronts on 1,024
+// SIMDs, so that half of these run two, and the other half wait for them.  Here a whole number of
+// blocks per CU takes `share` >= 256 consecutive lanes each and advances 256 of them at a time by q
+// steps, in turns: turn t runs the lanes t 256 .. t 256 + 255 modulo the share, so that every lane has
+// its steps after (steps / q) share / 256 turns and no SIMD waits.  Between its turns a lane is
+// parked in LDS (72 B).  The rule for taking this launch (turns_blocks) and its measurements are in
+// api.hip.
+template <bool HAM, bool UNIT_M, bool ZERO_A>
+__global__ void __launch_bounds__(256) rk4_f64_turns_kernel(IntArgs A, StTable T, int32_t share, int32_t q)
+{
+    extern __shared__ double park[];  // [8][share], then status and steps taken
+    int32_t *lane_st = (int32_t *)(park + 8 * share), *lane_taken = lane_st + share;
+    const int64_t base = (int64_t)blockIdx.x * share;
+    const int64_t rest = A.n - base;
+    const int32_t m = rest < share ? (int32_t)rest : share;  // lanes of this block (may be <= 0)
+    const int32_t t = (int32_t)threadIdx.x;
+    for (int32_t j = t; j < m; j += 256) {
+        lane_st[j] = A.status[base + j];
+        lane_taken[j] = 0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) park[k * share + j] = A.state[k * A.n + base + j];
+    }
+    __syncthreads();
+    Spacetime S = T.st[0];
+    if (UNIT_M) S.M = 1.0;
+    const int32_t runs = (A.n_steps + q - 1) / q;
+    // m >= 256: the turns tile the lanes in order; fewer lanes: each thread keeps its own
+    const int64_t turns = m >= 256 ? ((int64_t)runs * m + 255) / 256 : runs;
+    int32_t j = t;
+    for (int64_t turn = 0; turn < turns; ++turn) {
+        if (j < m && lane_st[j] == kActive && lane_taken[j] < A.n_steps) {
+            const int32_t taken = lane_taken[j], left = A.n_steps - taken;
+            int32_t st = kActive;
+            double y[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) y[k] = park[k * share + j];
+            const HamConst<double> P = ham_const(S.a, y[4], y[7]);
+            lane_taken[j] = taken + run_steps<HAM, ZERO_A>(S, P, A.h, A.r_escape, q < left ? q : left, y, st);
+            lane_st[j] = st;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) park[k * share + j] = y[k];
+        }
+        if (m >= 256) {
+            j += 256;
+            if (j >= m) j -= m;
+        }
+        __syncthreads();
+    }
+    for (int32_t i = t; i < m; i += 256) {
+        const int32_t taken = lane_taken[i];
+        if (taken > 0) {
+            A.status[base + i] = lane_st[i];
+            A.steps[base + i] += taken;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) A.state[k * A.n + base + i] = park[k * share + i];
+        }
+    }
+}
+
 // The FP64 step with the invariant monitor folded in every K steps: one thread per
 // lane, or the persistent work queue.
 template <bool HAM>
@@ -163,22 +222,35 @@ int launch_monitor(const IntArgs &A, const StTable &T, const MonArgs &MA, bool m
     return MALBEC_OK;
 }
 
-template <bool MULTI, bool CKPT, bool HAM>
-int launch_kernel(const IntArgs &A, const StTable &T, int block, hipStream_t s)
+template <bool HAM, bool UNIT_M, bool ZERO_A>
+int launch_uniform(const IntArgs &A, const StTable &T, int block, int32_t turns, hipStream_t s)
 {
-    constexpr bool kPlain = !MULTI && !CKPT;
-    if (kPlain && T.st[0].M == 1.0 && T.st[0].a == 0.0)
-        hipLaunchKernelGGL((rk4_f64_kernel<false, false, HAM, true, true>), dim3(grid_for(A.n, block)),
-                           dim3(block), 0, s, A, T);
-    else if (kPlain && T.st[0].a == 0.0)
-        hipLaunchKernelGGL((rk4_f64_kernel<false, false, HAM, false, true>), dim3(grid_for(A.n, block)),
-                           dim3(block), 0, s, A, T);
-    else if (kPlain && T.st[0].M == 1.0)
-        hipLaunchKernelGGL((rk4_f64_kernel<false, false, HAM, true>), dim3(grid_for(A.n, block)),
-                           dim3(block), 0, s, A, T);
-    else
-        hipLaunchKernelGGL((rk4_f64_kernel<MULTI, CKPT, HAM>), dim3(grid_for(A.n, block)), dim3(block),
-                           0, s, A, T);
+    if (turns > 0) {
+        const int32_t share = (int32_t)((A.n + turns - 1) / turns);
+        hipLaunchKernelGGL((rk4_f64_turns_kernel<HAM, UNIT_M, ZERO_A>), dim3(turns), dim3(256),
+                           (size_t)share * kTurnLaneBytes, s, A, T, share, kTurnSteps);
+        MALBEC_LAUNCH_CHECK("rk4_f64_turns_kernel");
+        return MALBEC_OK;
+    }
+    hipLaunchKernelGGL((rk4_f64_kernel<false, false, HAM, UNIT_M, ZERO_A>), dim3(grid_for(A.n, block)),
+                       dim3(block), 0, s, A, T);
+    MALBEC_LAUNCH_CHECK("rk4_f64_kernel");
+    return MALBEC_OK;
+}
+
+// turns: the blocks of a launch in turns, 0 for one thread per lane.
+template <bool MULTI, bool CKPT, bool HAM>
+int launch_kernel(const IntArgs &A, const StTable &T, int block, int32_t turns, hipStream_t s)
+{
+    if constexpr (!MULTI && !CKPT) {
+        const bool unit = T.st[0].M == 1.0, zero = T.st[0].a == 0.0;
+        if (zero) return unit ? launch_uniform<HAM, true, true>(A, T, block, turns, s)
+                              : launch_uniform<HAM, false, true>(A, T, block, turns, s);
+        return unit ? launch_uniform<HAM, true, false>(A, T, block, turns, s)
+                    : launch_uniform<HAM, false, false>(A, T, block, turns, s);
+    }
+    hipLaunchKernelGGL((rk4_f64_kernel<MULTI, CKPT, HAM>), dim3(grid_for(A.n, block)), dim3(block), 0, s,
+                       A, T);
     MALBEC_LAUNCH_CHECK("rk4_f64_kernel");
     return MALBEC_OK;
 }
@@ -223,16 +295,19 @@ int launch_integrate_f64(const malbec_run &run, const StTable &T, const int32_t 
     for (int64_t k0 = 0; k0 < total; k0 += chunk) {
         A.k0 = (int32_t)k0;
         A.n_steps = (int32_t)((total - k0) < chunk ? (total - k0) : chunk);
-        int rc;
+        int32_t turns = 0;
+        int rc = MALBEC_OK;
+        if (run.block == 0 && !multi && !A.ckpt) rc = turns_blocks(n, A.n_steps, turns);
+        if (rc) return rc;
         if (A.ckpt)
-            rc = multi ? launch_kernel<true, true, false>(A, T, block, s)
-                       : launch_kernel<false, true, false>(A, T, block, s);
+            rc = multi ? launch_kernel<true, true, false>(A, T, block, 0, s)
+                       : launch_kernel<false, true, false>(A, T, block, 0, s);
         else if (ham)
-            rc = multi ? launch_kernel<true, false, true>(A, T, block, s)
-                       : launch_kernel<false, false, true>(A, T, block, s);
+            rc = multi ? launch_kernel<true, false, true>(A, T, block, 0, s)
+                       : launch_kernel<false, false, true>(A, T, block, turns, s);
         else
-            rc = multi ? launch_kernel<true, false, false>(A, T, block, s)
-                       : launch_kernel<false, false, false>(A, T, block, s);
+            rc = multi ? launch_kernel<true, false, false>(A, T, block, 0, s)
+                       : launch_kernel<false, false, false>(A, T, block, turns, s);
         if (rc) return rc;
     }
     return MALBEC_OK;

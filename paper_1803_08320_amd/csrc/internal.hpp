@@ -60,6 +60,10 @@ int launch_monitor_f32k(const malbec_run &run, const StTable &T, const int32_t *
 // Grid of a persistent kernel: resident blocks per CU x CUs, capped by the blocks the
 // work needs.
 int persistent_grid(const void *kernel, int block, int64_t n_items, int &grid);
+// Launches in turns: LDS per lane, steps per turn, and the rule (blocks = 0: not in turns).
+constexpr int kTurnLaneBytes = 72;
+constexpr int32_t kTurnSteps = 16;
+int turns_blocks(int64_t n, int32_t n_steps, int32_t &blocks);
 int launch_camera(const malbec_camera &cam, double r_stop, double disk_r_in, int32_t *status,
                   int32_t *steps, double *hit, double *final_state, void *ws, hipStream_t s);
 int launch_adjoint(const malbec_run &run, const StTable &T, const int32_t *st_of_lane, int64_t n,

@@ -455,3 +455,29 @@ def test_schwarzschild_kernel_is_the_general_one(m, orc, formulation):
         np.testing.assert_array_equal(one[0], mixed[0][:, sel])
         np.testing.assert_array_equal(one[1], mixed[1][sel])
         np.testing.assert_array_equal(one[2], mixed[2][sel])
+
+
+@pytest.mark.parametrize("formulation", ["christoffel", "hamiltonian"])
+@pytest.mark.parametrize("n", [65537, 65536 + 77, 100003, 131072 + 1000, 196608 + 36000, 300007, 524288 + 1])
+def test_launch_in_turns_gives_the_bits_of_one_thread_per_lane(m, orc, formulation, n):
+    """Lane counts that fill the chip unevenly are launched in turns (block = 0); the bits,
+    status and steps are those of one thread per lane (block = 256): bound and plunging
+    lanes, lanes that are not active, any mass and spin, and a number of steps that is no
+    whole number of turns (100: the smallest that takes turns)."""
+    import torch
+    for k, (st, n_steps) in enumerate((((1.0, 0.9), 117), ((1.0, 0.0), 100), ((2.0, 1.3), 101),
+                                       ((0.5, 0.0), 128))):
+        state, _, _ = m.init_particles(spec_constants(m, 5 + k), [st], n)
+        state[5, ::97] = -30.0  # plunging
+        state[6, 5::1013] = float("nan")
+        status0, steps0 = m.new_lane_arrays(n)
+        status0[11::501] = 2
+        steps0 += 3
+        out = []
+        for block in (0, 256):
+            s, a, b = state.clone(), status0.clone(), steps0.clone()
+            m.integrate(s, a, b, [st], h=0.02, n_steps=n_steps, block=block, formulation=formulation)
+            out.append((s.view(torch.int64), a, b))
+        assert set(torch.unique(out[0][1]).tolist()) >= {0, 1, 2, 4}
+        for x, y in zip(*out):
+            assert torch.equal(x, y)
