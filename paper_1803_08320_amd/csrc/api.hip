@@ -53,9 +53,9 @@ int persistent_grid(const void *kernel, int block, int64_t n_items, int &grid)
 // steps, and the last one is partly idle: at 100 steps the gain at w + f = 1.5 and 4.6 is still 8 and
 // 2 %, at 64 steps it is within +-2 %, at 32 none, so from 100 steps on.  The parked lanes of four blocks
 // have to fit a CU's LDS, which ends it at w + f = 8.9.
-int turns_blocks(int64_t n, int32_t n_steps, int32_t &blocks)
+int turns_blocks(int64_t n, int64_t n_steps, int lane_bytes, int32_t &blocks, int32_t &per_cu)
 {
-    blocks = 0;
+    blocks = per_cu = 0;
     if (n_steps < 100) return MALBEC_OK;
     int dev = 0, n_cu = 0;
     MALBEC_HIP_CHECK(hipGetDevice(&dev));
@@ -63,9 +63,10 @@ int turns_blocks(int64_t n, int32_t n_steps, int32_t &blocks)
     const int64_t level = (int64_t)n_cu * 256;
     const int64_t w = n / level;
     if (w < 1 || n == w * level || (double)(n - w * level) > 0.55 * (double)level) return MALBEC_OK;
-    const int64_t per_cu = w < 4 ? w : 4, g = per_cu * n_cu;
+    const int64_t k = w < 4 ? w : 4, g = k * n_cu;
     const int64_t share = (n + g - 1) / g;
-    if (per_cu * share * kTurnLaneBytes > 160 * 1024) return MALBEC_OK;
+    if (k * share * lane_bytes > 160 * 1024) return MALBEC_OK;
+    per_cu = (int32_t)k;
     blocks = (int32_t)g;
     return MALBEC_OK;
 }

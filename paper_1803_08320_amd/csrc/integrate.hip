@@ -295,9 +295,9 @@ int launch_integrate_f64(const malbec_run &run, const StTable &T, const int32_t 
     for (int64_t k0 = 0; k0 < total; k0 += chunk) {
         A.k0 = (int32_t)k0;
         A.n_steps = (int32_t)((total - k0) < chunk ? (total - k0) : chunk);
-        int32_t turns = 0;
+        int32_t turns = 0, per_cu = 0;
         int rc = MALBEC_OK;
-        if (run.block == 0 && !multi && !A.ckpt) rc = turns_blocks(n, A.n_steps, turns);
+        if (run.block == 0 && !multi && !A.ckpt) rc = turns_blocks(n, A.n_steps, kTurnLaneBytes, turns, per_cu);
         if (rc) return rc;
         if (A.ckpt)
             rc = multi ? launch_kernel<true, true, false>(A, T, block, 0, s)

@@ -7,7 +7,9 @@
 // caller moves it off the device in chunks.
 //
 // Same step and stop rules as rk4_f64_kernel (either formulation).  One thread per
-// lane; the state stays in registers between records.
+// lane, the state in registers between records, or, where the lanes fill the chip
+// unevenly, in turns.
+#include "f64_prog.hpp"
 #include "internal.hpp"
 
 namespace malbec {
@@ -26,12 +28,6 @@ struct RecArgs {
     int32_t record_every;
     int32_t n_rec;
 };
-
-__device__ __forceinline__ void copy8(double dst[8], const double src[8])
-{
-#pragma unroll
-    for (int c = 0; c < 8; ++c) dst[c] = src[c];
-}
 
 // One step of either formulation from y into y1; returns the status and sets `accept`
 // (y1 is the lane's state after the step).
@@ -133,6 +129,68 @@ __global__ void __launch_bounds__(256) rk4_record_kernel(RecArgs A, StTable T)
     A.steps[ie] = steps0 + taken;
 }
 
+// The same in turns (rk4_f64_turns_kernel in integrate.hip); a turn is `per` whole record intervals.  A
+// lane that has stopped goes on to write its remaining records.  On one MI355X, a record every 20 of
+// 1,000 steps, one thread per lane and in turns: 70,000 lanes 1.57 and 1.05 ms, 100,003 lanes 1.59 and
+// 1.45, 150,000 lanes 2.29 and 1.93, Hamiltonian form 1.27 and 0.87, 1.28 and 1.21, 1.84 and 1.57.
+// Turns that end within an interval cost a second, short loop: 100,003 lanes 1.73 ms with 16 steps.
+// THREE: at least three blocks per CU, for which the Christoffel form (177 registers) and the
+// Hamiltonian one have to be held to three waves per SIMD; with fewer blocks that costs them 5 %.
+template <bool HAM, bool THREE>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(THREE ? 3 : 1, 8)))
+rk4_record_turns_kernel(RecArgs A, StTable T, int32_t share, int32_t per)
+{
+    extern __shared__ double park[];  // [8][share], then status, steps and records written
+    int32_t *lane_st = (int32_t *)(park + 8 * share), *lane_steps = lane_st + share,
+            *lane_rec = lane_steps + share;
+    const int64_t base = (int64_t)blockIdx.x * share;
+    const int64_t rest = A.n - base;
+    const int32_t m = rest < share ? (int32_t)rest : share;  // lanes of this block (may be <= 0)
+    const int32_t t = (int32_t)threadIdx.x;
+    for (int32_t j = t; j < m; j += 256) {
+        lane_st[j] = A.status[base + j];
+        lane_steps[j] = A.steps[base + j];
+        lane_rec[j] = 0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) park[k * share + j] = A.state[k * A.n + base + j];
+    }
+    __syncthreads();
+    const Spacetime S = T.st[0];
+    const int32_t runs = (A.n_rec + per - 1) / per;
+    const int64_t turns = m >= 256 ? ((int64_t)runs * m + 255) / 256 : runs;
+    int32_t j = t;
+    for (int64_t turn = 0; turn < turns; ++turn) {
+        if (j < m && lane_rec[j] < A.n_rec) {
+            int32_t st = lane_st[j], steps = lane_steps[j], rec = lane_rec[j];
+            const int32_t end = A.n_rec - rec < per ? A.n_rec : rec + per;
+            double y[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) y[k] = park[k * share + j];
+            const HamConst<double> P = ham_const(S.a, y[4], y[7]);
+            for (; rec < end; ++rec) {
+                if (st == kActive) steps += run_steps<HAM>(S, P, A.h, A.r_escape, A.record_every, y, st);
+                put_record(A, base + j, rec, S.a, y, steps);
+            }
+            lane_st[j] = st;
+            lane_steps[j] = steps;
+            lane_rec[j] = rec;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) park[k * share + j] = y[k];
+        }
+        if (m >= 256) {
+            j += 256;
+            if (j >= m) j -= m;
+        }
+        __syncthreads();
+    }
+    for (int32_t i = t; i < m; i += 256) {
+        A.status[base + i] = lane_st[i];
+        A.steps[base + i] = lane_steps[i];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) A.state[k * A.n + base + i] = park[k * share + i];
+    }
+}
+
 }  // namespace
 
 int launch_integrate_record(const malbec_run &run, const StTable &T, const int32_t *st_of_lane,
@@ -154,6 +212,32 @@ int launch_integrate_record(const malbec_run &run, const StTable &T, const int32
     A.r_escape = run.r_escape;
     A.record_every = record_every;
     A.n_rec = (int32_t)(run.n_steps / record_every);
+    // In turns from 8 steps per record on (a record costs about half a step, and a turn of 16 of them
+    // at every step no longer follows the rule's measurements: 100,003 lanes 0.28 and 0.32 ms), and
+    // where a lane has at least six turns (100,003 lanes, 2 records, 50 steps each: 0.20 and 0.24).
+    const int32_t per = (kTurnSteps + record_every - 1) / record_every;
+    if (run.block == 0 && !multi && record_every >= 8 && A.n_rec >= 6 * per) {
+        constexpr int kLaneBytes = kTurnLaneBytes + 4;
+        int32_t turns = 0, per_cu = 0;
+        const int rc = turns_blocks(n, run.n_steps, kLaneBytes, turns, per_cu);
+        if (rc) return rc;
+        if (turns > 0) {
+            const int32_t share = (int32_t)((n + turns - 1) / turns);
+            const bool three = per_cu >= 3;
+            const size_t lds = (size_t)share * kLaneBytes;
+            const dim3 g(turns), b(256);
+            if (ham && three)
+                hipLaunchKernelGGL((rk4_record_turns_kernel<true, true>), g, b, lds, s, A, T, share, per);
+            else if (ham)
+                hipLaunchKernelGGL((rk4_record_turns_kernel<true, false>), g, b, lds, s, A, T, share, per);
+            else if (three)
+                hipLaunchKernelGGL((rk4_record_turns_kernel<false, true>), g, b, lds, s, A, T, share, per);
+            else
+                hipLaunchKernelGGL((rk4_record_turns_kernel<false, false>), g, b, lds, s, A, T, share, per);
+            MALBEC_LAUNCH_CHECK("rk4_record_turns_kernel");
+            return MALBEC_OK;
+        }
+    }
     const dim3 grid(grid_for(n, block)), blk(block);
     if (multi && ham)
         hipLaunchKernelGGL((rk4_record_kernel<true, true>), grid, blk, 0, s, A, T);

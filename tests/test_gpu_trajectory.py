@@ -187,3 +187,29 @@ def test_stream_full_size_sampled(m, orc):
     assert good.mean() > 0.98
     err = np.abs(traj - ref_traj) / (np.abs(ref_traj) + 1.0)
     assert err[:, :, good].max() <= 1e-10
+
+
+@pytest.mark.parametrize("formulation", ["christoffel", "hamiltonian"])
+@pytest.mark.parametrize("n,every,n_rec", [(65537, 8, 13), (100003, 20, 7), (131072 + 900, 50, 6),
+                                           (196608 + 30000, 16, 7), (270001, 10, 13)])
+def test_records_in_turns_have_the_bits_of_one_thread_per_lane(m, orc, formulation, n, every, n_rec):
+    """Lane counts that fill the chip unevenly record in turns (block = 0): state, status,
+    steps and records equal those of one thread per lane (block = 256), with lanes that
+    plunge, that are not finite and that are not active, and odd numbers of records."""
+    import torch
+    st = [(1.0, 0.9)]
+    state, _, _ = m.init_particles(m.ICSpec(mode=m.IC_CONSTANTS, seed=6), st, n)
+    state[5, ::97] = -30.0
+    state[6, 5::1013] = float("nan")
+    status0, steps0 = m.new_lane_arrays(n)
+    status0[11::501] = 2
+    steps0 += 3
+    out = []
+    for block in (0, 256):
+        s, a, b = state.clone(), status0.clone(), steps0.clone()
+        traj = m.integrate_record(s, a, b, st, 0.02, n_rec * every, every, block=block,
+                                  formulation=formulation)
+        out.append((s.view(torch.int64), a, b, traj.view(torch.int64)))
+    assert set(torch.unique(out[0][1]).tolist()) >= {0, 1, 2, 4}
+    for x, y in zip(*out):
+        assert torch.equal(x, y)
