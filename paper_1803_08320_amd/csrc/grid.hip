@@ -221,26 +221,15 @@ __device__ __forceinline__ void grid_ham(const GridArgs &A, const HamConst<doubl
     dpth = fma(A.idth, force(Ft), (w2 * sc) * F[4]);
 }
 
-// At most 256 registers, the two waves per SIMD that the stencils' LDS allows.
+// Up to n_steps steps of an active lane from y, which receives its state after them; returns
+// the steps evaluated and sets st.
 template <typename Node>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-rk4_grid_kernel(GridArgs A)
+__device__ __forceinline__ int32_t grid_steps(const GridArgs &A, const HamConst<double> &P, Stencil &C,
+                                              int32_t n_steps, double y[8], int32_t &st)
 {
-    extern __shared__ Double2 lds_stencil[];
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= A.n) return;
-    int32_t st = A.status[i];
-    if (st != kActive) return;
-    double y[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) y[k] = A.state[k * A.n + i];
-    const HamConst<double> P{y[4], y[7], 0.0, 0.0};
-    Stencil C;
-    C.lds = &lds_stencil[(threadIdx.x / 64u) * (kLdsChunks * 64) + threadIdx.x % 64u];
-    C.ci = C.cj = -1;
     int32_t taken = 0;
     const double hh = 0.5 * A.h, h6 = A.h * (1.0 / 6.0);
-    while (taken < A.n_steps) {
+    while (taken < n_steps) {
         // One RK4 step, its stages in a loop: one copy of the right-hand side, so that the
         // stencil's registers have one place each.  The stop rules at the stage points: the
         // first that is in the stop zone or off the grid decides.
@@ -291,11 +280,81 @@ rk4_grid_kernel(GridArgs A)
         for (int c = 0; c < 8; ++c) y[c] = y1[c];
         if (st != kActive) break;
     }
+    return taken;
+}
+
+// At most 256 registers, the two waves per SIMD that the stencils' LDS allows.
+template <typename Node>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+rk4_grid_kernel(GridArgs A)
+{
+    extern __shared__ Double2 lds_stencil[];
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= A.n) return;
+    int32_t st = A.status[i];
+    if (st != kActive) return;
+    double y[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) y[k] = A.state[k * A.n + i];
+    const HamConst<double> P{y[4], y[7], 0.0, 0.0};
+    Stencil C;
+    C.lds = &lds_stencil[(threadIdx.x / 64u) * (kLdsChunks * 64) + threadIdx.x % 64u];
+    C.ci = C.cj = -1;
+    const int32_t taken = grid_steps<Node>(A, P, C, A.n_steps, y, st);
     const int64_t ie = opaque(i);
 #pragma unroll
     for (int k = 0; k < 8; ++k) A.state[k * A.n + ie] = y[k];
     A.status[ie] = st;
     A.steps[ie] += taken;
+}
+
+// A batch that fills the chip unevenly, in turns (rk4_f64_turns_kernel in integrate.hip).  The stencils
+// take the LDS, so the lanes that wait are parked where they came from, in the state arrays (L2).
+// The threads of a turn are a run of the sequence 0, 1, .. m - 1, 0, 1, ..: lane j has had
+// position / m turns, each of q steps while it was active.
+template <typename Node>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+rk4_grid_turns_kernel(GridArgs A, int32_t share, int32_t q)
+{
+    extern __shared__ Double2 lds_stencil[];
+    const int64_t base = (int64_t)blockIdx.x * share;
+    const int64_t rest = A.n - base;
+    const int32_t m = rest < share ? (int32_t)rest : share;  // lanes of this block (may be <= 0)
+    const int32_t runs = (A.n_steps + q - 1) / q;
+    const int64_t turns = m >= 256 ? ((int64_t)runs * m + 255) / 256 : runs;
+    Stencil C;
+    C.lds = &lds_stencil[(threadIdx.x / 64u) * (kLdsChunks * 64) + threadIdx.x % 64u];
+    int32_t j = (int32_t)threadIdx.x, gone = 0;  // the lane, and the steps it has had if active
+    for (int64_t turn = 0; turn < turns; ++turn) {
+        if (j < m && gone < A.n_steps) {
+            const int64_t i = base + j;
+            int32_t st = A.status[i];
+            if (st == kActive) {
+                double y[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) y[k] = A.state[k * A.n + i];
+                const HamConst<double> P{y[4], y[7], 0.0, 0.0};
+                C.ci = C.cj = -1;
+                const int32_t left = A.n_steps - gone;
+                const int32_t taken = grid_steps<Node>(A, P, C, q < left ? q : left, y, st);
+                const int64_t ie = opaque(i);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) A.state[k * A.n + ie] = y[k];
+                A.status[ie] = st;
+                A.steps[ie] += taken;
+            }
+        }
+        if (m < 256) {
+            gone += q;
+        } else {
+            j += 256;
+            if (j >= m) {
+                j -= m;
+                gone += q;
+            }
+        }
+        __syncthreads();
+    }
 }
 
 // Kerr's 3+1 functions (Section 2) at every node, computed in FP64 and stored as Node.
@@ -338,6 +397,30 @@ int launch_grid_fill_kerr(const malbec_grid &g, double M, double a, void *nodes,
     return MALBEC_OK;
 }
 
+// The blocks of a launch in turns, 0 where one thread per lane is the better launch.  With
+// n / (256 lanes per CU) = w + f, w whole, min(w, 2) blocks per CU (their stencils fill its LDS).  A turn
+// gathers every lane's stencil again, so it is worth less here than where lanes park in LDS.  One
+// thread per lane and in turns on one MI355X, ms (400 steps, 801 x 401 double and 401 x 201 float nodes;
+// 100 steps, double nodes):
+//   w + f   1.05          1.3           1.5           2.05          2.5           3.05          3.5
+//         2.87 2.26     2.93 2.77     2.96 3.18     4.67 3.66     4.63 4.34     6.04 5.32     6.06 6.03
+//         2.76 1.99     2.77 2.43     2.79 2.78     4.22 3.31     4.27 3.87     5.70 4.84     5.60 5.43
+//         0.76 0.66     0.77 0.78     0.77 0.87     1.14 0.99     1.15 1.13     1.47 1.39     1.48 1.57
+// Turns of 32 steps, of 16 below 160 (at 400 steps 16 is 3-5 % slower, at 100 32 is 5 % slower).
+static int grid_turns(int64_t n, int32_t n_steps, int32_t &blocks)
+{
+    blocks = 0;
+    if (n_steps < 100) return MALBEC_OK;
+    int dev = 0, n_cu = 0;
+    MALBEC_HIP_CHECK(hipGetDevice(&dev));
+    MALBEC_HIP_CHECK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
+    const int64_t level = (int64_t)n_cu * 256, w = n / level;
+    const double f = (double)(n - w * level) / (double)level;
+    const double most = w == 1 ? 0.25 : w == 2 ? 0.5 : w == 3 ? 0.3 : 0.0;
+    if (f > 0.0 && f <= most) blocks = (int32_t)(w < 2 ? n_cu : 2 * n_cu);
+    return MALBEC_OK;
+}
+
 int launch_integrate_grid(const malbec_run &run, const malbec_grid &g, int64_t n, double *state,
                           int32_t *status, int32_t *steps, hipStream_t s)
 {
@@ -371,6 +454,21 @@ int launch_integrate_grid(const malbec_run &run, const malbec_grid &g, int64_t n
     const int64_t chunk = run.steps_per_chunk > 0 ? run.steps_per_chunk : total;
     for (int64_t k0 = 0; k0 < total; k0 += chunk) {
         A.n_steps = (int32_t)((total - k0) < chunk ? (total - k0) : chunk);
+        int32_t turns = 0;
+        if (run.block == 0) {
+            const int rc = grid_turns(n, A.n_steps, turns);
+            if (rc) return rc;
+        }
+        if (turns > 0) {
+            const int32_t share = (int32_t)((n + turns - 1) / turns);
+            const int32_t q = A.n_steps < 160 ? 16 : 32;
+            if (g.node_precision == MALBEC_GRID_F32)
+                hipLaunchKernelGGL(rk4_grid_turns_kernel<float>, dim3(turns), dim3(256), lds, s, A, share, q);
+            else
+                hipLaunchKernelGGL(rk4_grid_turns_kernel<double>, dim3(turns), dim3(256), lds, s, A, share, q);
+            MALBEC_LAUNCH_CHECK("rk4_grid_turns_kernel");
+            continue;
+        }
         if (g.node_precision == MALBEC_GRID_F32)
             hipLaunchKernelGGL(rk4_grid_kernel<float>, dim3(grid_for(n, block)), dim3(block), lds, s, A);
         else

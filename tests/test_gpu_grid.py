@@ -258,3 +258,31 @@ def test_smallest_grids_and_ragged_blocks(m, orc, nr, nth, n, block, f32):
     ref = orc.integrate_grid(G, z0, 0.05, 400, r_stop=r_stop, r_escape=r_esc)
     compare(orc, st, z0, *got, *ref,
             lambda p0: orc.integrate_grid(G, p0, 0.05, 400, r_stop=r_stop, r_escape=r_esc))
+
+
+@pytest.mark.parametrize("node_dtype", ["float64", "float32"])
+@pytest.mark.parametrize("n,n_steps", [(65537, 100), (80000, 170), (131072 + 77, 101), (160000, 120),
+                                       (196608 + 9000, 165)])
+def test_grid_launch_in_turns_has_the_bits_of_one_thread_per_lane(m, orc, node_dtype, n, n_steps):
+    """Lane counts that fill the chip unevenly are launched in turns (block = 0); the bits,
+    status and steps are those of one thread per lane (block = 256), with lanes that plunge or
+    leave the grid, that are not finite and that are not active."""
+    import torch
+    g = m.grid_kerr(1.0, 0.9, 401, 201, 1.5, 60.0 / 400, 0.1, (math.pi - 0.2) / 200, 1.2 * r_plus(0.9),
+                    node_dtype=getattr(torch, node_dtype))
+    state, _, _ = m.init_particles(m.ICSpec(mode=m.IC_CONSTANTS, seed=6), [(1.0, 0.9)], n)
+    m.convert_state(state, [(1.0, 0.9)], True)
+    state[5, ::97] = -30.0
+    state[5, 1::97] = 30.0
+    state[6, 5::1013] = float("nan")
+    status0, steps0 = m.new_lane_arrays(n)
+    status0[11::501] = 2
+    steps0 += 3
+    out = []
+    for block in (0, 256):
+        s, a, b = state.clone(), status0.clone(), steps0.clone()
+        m.integrate_grid(s, a, b, g, 0.02, n_steps, 40.0, block=block)
+        out.append((s.view(torch.int64), a, b))
+    assert set(torch.unique(out[0][1]).tolist()) >= {0, 1, 2, 4}
+    for x, y in zip(*out):
+        assert torch.equal(x, y)
