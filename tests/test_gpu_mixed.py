@@ -293,9 +293,9 @@ def test_mixed_full_size_sampled(m, orc):
 @pytest.mark.parametrize("form", ["christoffel", "hamiltonian"])
 @pytest.mark.parametrize("persistent", [False, True])
 def test_steps_in_pairs_next_to_the_limits(m, orc, form, persistent):
-    """A launch that takes FP32 steps in pairs, under single-precision tests, gives the bits
-    of one that hands out single steps, which take the full rules: lanes within an ulp or a
-    step of the FP64 zone, of the escape radius and of the poles, lanes that plunge, and
+    """A launch that takes FP32 steps in pairs, or tests their common outcome first in single
+    precision, gives the bits of one that hands out single steps, and of the monitored
+    integration, whose steps take the full rules: lanes within an ulp or a step of the FP64 zone, of the escape radius and of the poles, lanes that plunge, and
     lanes that are not finite; odd and even numbers of steps."""
     import torch
     st = [(1.0, 0.9), (1.0, 0.0)]
@@ -325,9 +325,18 @@ def test_steps_in_pairs_next_to_the_limits(m, orc, form, persistent):
                     st_of_lane=torch.as_tensor(sol).cuda(), steps_per_chunk=steps_per_chunk, **kw)
         return state.cpu().numpy(), status.cpu().numpy(), steps.cpu().numpy()
 
+    def full_rules(n_steps):
+        state = torch.as_tensor(s0).cuda()
+        status = torch.zeros(n, dtype=torch.int32, device="cuda")
+        steps = torch.zeros(n, dtype=torch.int32, device="cuda")
+        m.integrate_monitored(state, status, steps, st, 0.05, n_steps, 1000,
+                              st_of_lane=torch.as_tensor(sol).cuda(), **kw)
+        return state.cpu().numpy(), status.cpu().numpy(), steps.cpu().numpy()
+
     for n_steps in (1, 2, 3, 40, 41):
-        got, ref = go(n_steps, persistent, 0), go(n_steps, True, 1)
-        np.testing.assert_array_equal(got[0], ref[0])  # NaN equals NaN here, no tolerance
-        np.testing.assert_array_equal(got[1], ref[1])
-        np.testing.assert_array_equal(got[2], ref[2])
+        got = go(n_steps, persistent, 0)
+        for ref in (go(n_steps, True, 1), full_rules(n_steps)):
+            np.testing.assert_array_equal(got[0], ref[0])  # NaN equals NaN here, no tolerance
+            np.testing.assert_array_equal(got[1], ref[1])
+            np.testing.assert_array_equal(got[2], ref[2])
     assert set(np.unique(got[1])) >= {0, 1, 2, 4}
