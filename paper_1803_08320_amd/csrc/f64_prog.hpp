@@ -151,12 +151,14 @@ __global__ void __launch_bounds__(256) rk4_f64_persistent_kernel(IntArgs A, StTa
 }
 
 template <bool MULTI, bool HAM>
-int launch_persistent(const IntArgs &A, const StTable &T, int block, int32_t sub,
+int launch_persistent(const IntArgs &A, const StTable &T, int block, int32_t sub, bool &declined,
                       unsigned long long *counter, hipStream_t s)
 {
     int grid = 0;
     int rc = persistent_grid((const void *)rk4_f64_persistent_kernel<MULTI, HAM>, block, A.n, grid);
     if (rc) return rc;
+    declined = declined && queue_is_idle(A.n, grid, block);
+    if (declined) return MALBEC_OK;
     hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(1), 0, s, counter);
     MALBEC_LAUNCH_CHECK("zero_u64_kernel");
     hipLaunchKernelGGL((rk4_f64_persistent_kernel<MULTI, HAM>), dim3(grid), dim3(block), 0, s, A, T,
@@ -167,8 +169,9 @@ int launch_persistent(const IntArgs &A, const StTable &T, int block, int32_t sub
 
 }  // namespace
 
-// The persistent kernel of the Christoffel form (queue.hip).
+// The persistent kernel of the Christoffel form (queue.hip).  declined: in, whether the launch
+// may be left to one thread per lane; out, whether it was.
 int launch_queue_f64(const IntArgs &A, const StTable &T, bool multi, int block, int32_t sub,
-                     unsigned long long *counter, hipStream_t s);
+                     bool &declined, unsigned long long *counter, hipStream_t s);
 
 }  // namespace malbec

@@ -203,18 +203,21 @@ __global__ void __launch_bounds__(256) rk4_f64_monitor_persistent_kernel(IntArgs
 
 template <bool HAM>
 int launch_monitor(const IntArgs &A, const StTable &T, const MonArgs &MA, bool multi, int block,
-                   bool persistent, int32_t sub, unsigned long long *counter, hipStream_t s)
+                   bool persistent, bool may_decline, int32_t sub, unsigned long long *counter,
+                   hipStream_t s)
 {
     if (persistent) {
         int grid = 0;
         int rc = persistent_grid((const void *)rk4_f64_monitor_persistent_kernel<HAM>, block, A.n, grid);
         if (rc) return rc;
-        hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(1), 0, s, counter);
-        MALBEC_LAUNCH_CHECK("zero_u64_kernel");
-        hipLaunchKernelGGL((rk4_f64_monitor_persistent_kernel<HAM>), dim3(grid), dim3(block), 0, s,
-                           A, T, MA, (int32_t)multi, counter, sub);
-        MALBEC_LAUNCH_CHECK("rk4_f64_monitor_persistent_kernel");
-        return MALBEC_OK;
+        if (!(may_decline && queue_is_idle(A.n, grid, block))) {
+            hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(1), 0, s, counter);
+            MALBEC_LAUNCH_CHECK("zero_u64_kernel");
+            hipLaunchKernelGGL((rk4_f64_monitor_persistent_kernel<HAM>), dim3(grid), dim3(block), 0, s,
+                               A, T, MA, (int32_t)multi, counter, sub);
+            MALBEC_LAUNCH_CHECK("rk4_f64_monitor_persistent_kernel");
+            return MALBEC_OK;
+        }
     }
     hipLaunchKernelGGL((rk4_f64_monitor_kernel<HAM>), dim3(grid_for(A.n, block)), dim3(block), 0, s,
                        A, T, MA, (int32_t)multi);
@@ -287,10 +290,14 @@ int launch_integrate_f64(const malbec_run &run, const StTable &T, const int32_t 
         A.n_steps = (int32_t)total;
         const int32_t sub = run.steps_per_chunk > 0 ? run.steps_per_chunk : 64;
         unsigned long long *counter = (unsigned long long *)ws;
-        if (ham)
-            return multi ? launch_persistent<true, true>(A, T, block, sub, counter, s)
-                         : launch_persistent<false, true>(A, T, block, sub, counter, s);
-        return launch_queue_f64(A, T, multi, block, sub, counter, s);
+        bool declined = run.block == 0 && run.steps_per_chunk == 0;
+        int rc;
+        if (!ham)
+            rc = launch_queue_f64(A, T, multi, block, sub, declined, counter, s);
+        else
+            rc = multi ? launch_persistent<true, true>(A, T, block, sub, declined, counter, s)
+                       : launch_persistent<false, true>(A, T, block, sub, declined, counter, s);
+        if (rc || !declined) return rc;
     }
     for (int64_t k0 = 0; k0 < total; k0 += chunk) {
         A.k0 = (int32_t)k0;
@@ -339,16 +346,17 @@ int launch_monitor_f64(const malbec_run &run, const StTable &T, const int32_t *s
     if (run.persistent) {
         A.n_steps = (int32_t)total;
         const int32_t sub = run.steps_per_chunk > 0 ? run.steps_per_chunk : 64;
-        return ham ? launch_monitor<true>(A, T, MA, multi, block, true, sub, counter, s)
-                   : launch_monitor<false>(A, T, MA, multi, block, true, sub, counter, s);
+        const bool may_decline = run.block == 0 && run.steps_per_chunk == 0;
+        return ham ? launch_monitor<true>(A, T, MA, multi, block, true, may_decline, sub, counter, s)
+                   : launch_monitor<false>(A, T, MA, multi, block, true, may_decline, sub, counter, s);
     }
     const int64_t chunk = run.steps_per_chunk > 0 ? run.steps_per_chunk : total;
     for (int64_t k0 = 0; k0 < total; k0 += chunk) {
         A.k0 = (int32_t)k0;
         A.n_steps = (int32_t)((total - k0) < chunk ? (total - k0) : chunk);
         MA.reset = (k0 == 0) ? reset : 0;
-        int rc = ham ? launch_monitor<true>(A, T, MA, multi, block, false, 0, counter, s)
-                     : launch_monitor<false>(A, T, MA, multi, block, false, 0, counter, s);
+        int rc = ham ? launch_monitor<true>(A, T, MA, multi, block, false, false, 0, counter, s)
+                     : launch_monitor<false>(A, T, MA, multi, block, false, false, 0, counter, s);
         if (rc) return rc;
     }
     return MALBEC_OK;

@@ -425,18 +425,21 @@ rk4_f32k_monitor_persistent_kernel(MixArgs A, StTable T, MonArgs MA, int32_t mul
 
 template <bool HAM>
 int launch_monitor(const MixArgs &A, const StTable &T, const MonArgs &MA, bool multi, int block,
-                   bool persistent, int32_t sub, unsigned long long *counter, hipStream_t s)
+                   bool persistent, bool may_decline, int32_t sub, unsigned long long *counter,
+                   hipStream_t s)
 {
     if (persistent) {
         int grid = 0;
         int rc = persistent_grid((const void *)rk4_f32k_monitor_persistent_kernel<HAM>, block, A.n, grid);
         if (rc) return rc;
-        hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(1), 0, s, counter);
-        MALBEC_LAUNCH_CHECK("zero_u64_kernel");
-        hipLaunchKernelGGL((rk4_f32k_monitor_persistent_kernel<HAM>), dim3(grid), dim3(block), 0, s,
-                           A, T, MA, (int32_t)multi, counter, sub);
-        MALBEC_LAUNCH_CHECK("rk4_f32k_monitor_persistent_kernel");
-        return MALBEC_OK;
+        if (!(may_decline && queue_is_idle(A.n, grid, block))) {
+            hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(1), 0, s, counter);
+            MALBEC_LAUNCH_CHECK("zero_u64_kernel");
+            hipLaunchKernelGGL((rk4_f32k_monitor_persistent_kernel<HAM>), dim3(grid), dim3(block), 0, s,
+                               A, T, MA, (int32_t)multi, counter, sub);
+            MALBEC_LAUNCH_CHECK("rk4_f32k_monitor_persistent_kernel");
+            return MALBEC_OK;
+        }
     }
     hipLaunchKernelGGL((rk4_f32k_monitor_kernel<HAM>), dim3(grid_for(A.n, block)), dim3(block), 0, s,
                        A, T, MA, (int32_t)multi);
@@ -447,20 +450,22 @@ int launch_monitor(const MixArgs &A, const StTable &T, const MonArgs &MA, bool m
 }  // namespace
 
 template <bool MULTI, bool HAM>
-int launch_f32k(const MixArgs &A, const StTable &T, bool persistent, int32_t sub, int block,
+int launch_f32k(const MixArgs &A, const StTable &T, bool persistent, bool may_decline, int32_t sub, int block,
                 void *ws, hipStream_t s)
 {
     if (persistent) {
         int grid = 0;
         int rc = persistent_grid((const void *)rk4_f32k_persistent_kernel<MULTI, HAM>, block, A.n, grid);
         if (rc) return rc;
-        unsigned long long *counter = (unsigned long long *)ws;
-        hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(1), 0, s, counter);
-        MALBEC_LAUNCH_CHECK("zero_u64_kernel");
-        hipLaunchKernelGGL((rk4_f32k_persistent_kernel<MULTI, HAM>), dim3(grid), dim3(block), 0, s,
-                           A, T, counter, sub);
-        MALBEC_LAUNCH_CHECK("rk4_f32k_persistent_kernel");
-        return MALBEC_OK;
+        if (!(may_decline && queue_is_idle(A.n, grid, block))) {
+            unsigned long long *counter = (unsigned long long *)ws;
+            hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(1), 0, s, counter);
+            MALBEC_LAUNCH_CHECK("zero_u64_kernel");
+            hipLaunchKernelGGL((rk4_f32k_persistent_kernel<MULTI, HAM>), dim3(grid), dim3(block), 0, s,
+                               A, T, counter, sub);
+            MALBEC_LAUNCH_CHECK("rk4_f32k_persistent_kernel");
+            return MALBEC_OK;
+        }
     }
     hipLaunchKernelGGL((rk4_f32k_kernel<MULTI, HAM>), dim3(grid_for(A.n, block)), dim3(block), 0, s,
                        A, T);
@@ -486,12 +491,13 @@ int launch_integrate_f32k(const malbec_run &run, const StTable &T, const int32_t
     A.h = run.h;
     A.r_escape = run.r_escape;
     A.r_escape_safe = safe_below(run.r_escape);
+    const bool may_decline = run.block == 0 && run.steps_per_chunk == 0;
     auto go = [&](bool persistent, int32_t sub) {
         if (multi)
-            return ham ? launch_f32k<true, true>(A, T, persistent, sub, block, ws, s)
-                       : launch_f32k<true, false>(A, T, persistent, sub, block, ws, s);
-        return ham ? launch_f32k<false, true>(A, T, persistent, sub, block, ws, s)
-                   : launch_f32k<false, false>(A, T, persistent, sub, block, ws, s);
+            return ham ? launch_f32k<true, true>(A, T, persistent, may_decline, sub, block, ws, s)
+                       : launch_f32k<true, false>(A, T, persistent, may_decline, sub, block, ws, s);
+        return ham ? launch_f32k<false, true>(A, T, persistent, may_decline, sub, block, ws, s)
+                   : launch_f32k<false, false>(A, T, persistent, may_decline, sub, block, ws, s);
     };
     if (run.persistent) {
         A.n_steps = (int32_t)total;
@@ -529,15 +535,16 @@ int launch_monitor_f32k(const malbec_run &run, const StTable &T, const int32_t *
     if (run.persistent) {
         A.n_steps = (int32_t)total;
         const int32_t sub = run.steps_per_chunk > 0 ? run.steps_per_chunk : 64;
-        return ham ? launch_monitor<true>(A, T, MA, multi, block, true, sub, counter, s)
-                   : launch_monitor<false>(A, T, MA, multi, block, true, sub, counter, s);
+        const bool may_decline = run.block == 0 && run.steps_per_chunk == 0;
+        return ham ? launch_monitor<true>(A, T, MA, multi, block, true, may_decline, sub, counter, s)
+                   : launch_monitor<false>(A, T, MA, multi, block, true, may_decline, sub, counter, s);
     }
     const int64_t chunk = run.steps_per_chunk > 0 ? run.steps_per_chunk : total;
     for (int64_t k0 = 0; k0 < total; k0 += chunk) {
         A.n_steps = (int32_t)((total - k0) < chunk ? (total - k0) : chunk);
         MA.reset = (k0 == 0) ? reset : 0;
-        int rc = ham ? launch_monitor<true>(A, T, MA, multi, block, false, 0, counter, s)
-                     : launch_monitor<false>(A, T, MA, multi, block, false, 0, counter, s);
+        int rc = ham ? launch_monitor<true>(A, T, MA, multi, block, false, false, 0, counter, s)
+                     : launch_monitor<false>(A, T, MA, multi, block, false, false, 0, counter, s);
         if (rc) return rc;
     }
     return MALBEC_OK;

@@ -9,10 +9,10 @@
 namespace malbec {
 
 int launch_queue_f64(const IntArgs &A, const StTable &T, bool multi, int block, int32_t sub,
-                     unsigned long long *counter, hipStream_t s)
+                     bool &declined, unsigned long long *counter, hipStream_t s)
 {
-    return multi ? launch_persistent<true, false>(A, T, block, sub, counter, s)
-                 : launch_persistent<false, false>(A, T, block, sub, counter, s);
+    return multi ? launch_persistent<true, false>(A, T, block, sub, declined, counter, s)
+                 : launch_persistent<false, false>(A, T, block, sub, declined, counter, s);
 }
 
 }  // namespace malbec

@@ -334,9 +334,37 @@ def test_steps_in_pairs_next_to_the_limits(m, orc, form, persistent):
         return state.cpu().numpy(), status.cpu().numpy(), steps.cpu().numpy()
 
     for n_steps in (1, 2, 3, 40, 41):
-        got = go(n_steps, persistent, 0)
+        got = go(n_steps, persistent, 64 if persistent else 0)
         for ref in (go(n_steps, True, 1), full_rules(n_steps)):
             np.testing.assert_array_equal(got[0], ref[0])  # NaN equals NaN here, no tolerance
             np.testing.assert_array_equal(got[1], ref[1])
             np.testing.assert_array_equal(got[2], ref[2])
     assert set(np.unique(got[1])) >= {0, 1, 2, 4}
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32k"])
+@pytest.mark.parametrize("form", ["christoffel", "hamiltonian"])
+@pytest.mark.parametrize("n", [1, 1000, 196608, 196609, 262144, 262145])
+def test_queue_of_default_shape_has_the_bits_of_the_queue(m, orc, precision, form, n):
+    """A persistent launch of default shape whose lanes are all in flight at once is left to
+    one thread per lane; state, status, steps and monitor equal those of the queue (a given
+    steps_per_chunk), below, at and above the numbers of lanes that are resident (three and
+    four waves per SIMD)."""
+    import torch
+    state, _, _ = m.init_particles(m.ICSpec(mode=m.IC_CONSTANTS, seed=8), SPINS, n,
+                                   st_of_lane=torch.arange(n, dtype=torch.int32, device="cuda") % 16)
+    sol = torch.arange(n, dtype=torch.int32, device="cuda") % 16
+    sol[3::1001] = 99  # not a spacetime: the lane cannot step
+    state[5, 7::97] = -30.0
+    out = []
+    for chunk in (0, 16):
+        kw = dict(h=0.02, n_steps=45, st_of_lane=sol, persistent=True, steps_per_chunk=chunk,
+                  precision=precision, formulation=form)
+        s, (a, b) = state.clone(), m.new_lane_arrays(n)
+        m.integrate(s, a, b, SPINS, **kw)
+        s2, (a2, b2) = state.clone(), m.new_lane_arrays(n)
+        mon = m.integrate_monitored(s2, a2, b2, SPINS, monitor_every=10, **kw)
+        out.append([x.view(torch.int64) if x.dtype == torch.float64 else x
+                    for x in (s, a, b, s2, a2, b2, torch.nan_to_num(mon))])
+    for x, y in zip(*out):
+        assert torch.equal(x, y)
