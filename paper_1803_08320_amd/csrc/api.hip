@@ -49,7 +49,8 @@ int persistent_grid(const void *kernel, int block, int64_t n_items, int &grid)
 //   w + f   3.6            4.0 (263,454)  4.6            5.3            6.5            8.1
 //         2.86 2.73      3.61 2.99      3.58 3.41      4.29 3.92      5.03 4.84      6.50 6.06
 //         2.27 2.16      2.85 2.39      2.82 2.73      3.38 3.14      3.96 3.91      5.13 4.89
-// So in turns for f up to 0.55 (f = 0.8: even, or 2 % slower).  A turn costs about 0.4 us besides its
+// So in turns for f up to 0.55 with one block per CU and 0.6 with more (f = 0.8: even, or 2 % slower);
+// a batch of 16 spacetimes gains as much.  A turn costs about 0.4 us besides its
 // steps, and the last one is partly idle: at 100 steps the gain at w + f = 1.5 and 4.6 is still 8 and
 // 2 %, at 64 steps it is within +-2 %, at 32 none, so from 100 steps on.  The parked lanes of four blocks
 // have to fit a CU's LDS, which ends it at w + f = 8.9.
@@ -62,7 +63,7 @@ int turns_blocks(int64_t n, int64_t n_steps, int lane_bytes, int32_t &blocks, in
     MALBEC_HIP_CHECK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
     const int64_t level = (int64_t)n_cu * 256;
     const int64_t w = n / level;
-    if (w < 1 || n == w * level || (double)(n - w * level) > 0.55 * (double)level) return MALBEC_OK;
+    if (w < 1 || n == w * level || (double)(n - w * level) > (w == 1 ? 0.55 : 0.6) * (double)level) return MALBEC_OK;
     const int64_t k = w < 4 ? w : 4, g = k * n_cu;
     const int64_t share = (n + g - 1) / g;
     if (k * share * lane_bytes > 160 * 1024) return MALBEC_OK;

@@ -115,9 +115,12 @@ __global__ void __launch_bounds__(256) rk4_f64_kernel(IntArgs A, StTable T)
 // its steps after (steps / q) share / 256 turns and no SIMD waits.  Between its turns a lane is
 // parked in LDS (72 B).  The rule for taking this launch (turns_blocks) and its measurements are in
 // api.hip.
-template <bool HAM, bool UNIT_M, bool ZERO_A>
+template <bool MULTI, bool HAM, bool UNIT_M, bool ZERO_A>
 __global__ void __launch_bounds__(256) rk4_f64_turns_kernel(IntArgs A, StTable T, int32_t share, int32_t q)
 {
+    __shared__ Spacetime lds_st[MULTI ? kMaxSt : 1];
+    if (MULTI)
+        for (int k = threadIdx.x; k < T.n_st; k += blockDim.x) lds_st[k] = T.st[k];
     extern __shared__ double park[];  // [8][share], then status and steps taken
     int32_t *lane_st = (int32_t *)(park + 8 * share), *lane_taken = lane_st + share;
     const int64_t base = (int64_t)blockIdx.x * share;
@@ -125,7 +128,15 @@ __global__ void __launch_bounds__(256) rk4_f64_turns_kernel(IntArgs A, StTable T
     const int32_t m = rest < share ? (int32_t)rest : share;  // lanes of this block (may be <= 0)
     const int32_t t = (int32_t)threadIdx.x;
     for (int32_t j = t; j < m; j += 256) {
-        lane_st[j] = A.status[base + j];
+        int32_t st = A.status[base + j];
+        if (MULTI) {
+            const int32_t sid = A.st_of_lane[base + j];
+            if (sid < 0 || sid >= T.n_st) {  // invalid spacetime index: the lane cannot step
+                if (st == kActive) st = kNonfinite;
+                A.status[base + j] = st;
+            }
+        }
+        lane_st[j] = st;
         lane_taken[j] = 0;
 #pragma unroll
         for (int k = 0; k < 8; ++k) park[k * share + j] = A.state[k * A.n + base + j];
@@ -144,6 +155,7 @@ __global__ void __launch_bounds__(256) rk4_f64_turns_kernel(IntArgs A, StTable T
             double y[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k) y[k] = park[k * share + j];
+            if (MULTI) S = lds_st[A.st_of_lane[base + j]];
             const HamConst<double> P = ham_const(S.a, y[4], y[7]);
             lane_taken[j] = taken + run_steps<HAM, ZERO_A>(S, P, A.h, A.r_escape, q < left ? q : left, y, st);
             lane_st[j] = st;
@@ -225,17 +237,17 @@ int launch_monitor(const IntArgs &A, const StTable &T, const MonArgs &MA, bool m
     return MALBEC_OK;
 }
 
-template <bool HAM, bool UNIT_M, bool ZERO_A>
-int launch_uniform(const IntArgs &A, const StTable &T, int block, int32_t turns, hipStream_t s)
+template <bool MULTI, bool HAM, bool UNIT_M, bool ZERO_A>
+int launch_plain(const IntArgs &A, const StTable &T, int block, int32_t turns, hipStream_t s)
 {
     if (turns > 0) {
         const int32_t share = (int32_t)((A.n + turns - 1) / turns);
-        hipLaunchKernelGGL((rk4_f64_turns_kernel<HAM, UNIT_M, ZERO_A>), dim3(turns), dim3(256),
+        hipLaunchKernelGGL((rk4_f64_turns_kernel<MULTI, HAM, UNIT_M, ZERO_A>), dim3(turns), dim3(256),
                            (size_t)share * kTurnLaneBytes, s, A, T, share, kTurnSteps);
         MALBEC_LAUNCH_CHECK("rk4_f64_turns_kernel");
         return MALBEC_OK;
     }
-    hipLaunchKernelGGL((rk4_f64_kernel<false, false, HAM, UNIT_M, ZERO_A>), dim3(grid_for(A.n, block)),
+    hipLaunchKernelGGL((rk4_f64_kernel<MULTI, false, HAM, UNIT_M, ZERO_A>), dim3(grid_for(A.n, block)),
                        dim3(block), 0, s, A, T);
     MALBEC_LAUNCH_CHECK("rk4_f64_kernel");
     return MALBEC_OK;
@@ -245,12 +257,13 @@ int launch_uniform(const IntArgs &A, const StTable &T, int block, int32_t turns,
 template <bool MULTI, bool CKPT, bool HAM>
 int launch_kernel(const IntArgs &A, const StTable &T, int block, int32_t turns, hipStream_t s)
 {
+    if constexpr (MULTI && !CKPT) return launch_plain<true, HAM, false, false>(A, T, block, turns, s);
     if constexpr (!MULTI && !CKPT) {
         const bool unit = T.st[0].M == 1.0, zero = T.st[0].a == 0.0;
-        if (zero) return unit ? launch_uniform<HAM, true, true>(A, T, block, turns, s)
-                              : launch_uniform<HAM, false, true>(A, T, block, turns, s);
-        return unit ? launch_uniform<HAM, true, false>(A, T, block, turns, s)
-                    : launch_uniform<HAM, false, false>(A, T, block, turns, s);
+        if (zero) return unit ? launch_plain<false, HAM, true, true>(A, T, block, turns, s)
+                              : launch_plain<false, HAM, false, true>(A, T, block, turns, s);
+        return unit ? launch_plain<false, HAM, true, false>(A, T, block, turns, s)
+                    : launch_plain<false, HAM, false, false>(A, T, block, turns, s);
     }
     hipLaunchKernelGGL((rk4_f64_kernel<MULTI, CKPT, HAM>), dim3(grid_for(A.n, block)), dim3(block), 0, s,
                        A, T);
@@ -304,16 +317,16 @@ int launch_integrate_f64(const malbec_run &run, const StTable &T, const int32_t 
         A.n_steps = (int32_t)((total - k0) < chunk ? (total - k0) : chunk);
         int32_t turns = 0, per_cu = 0;
         int rc = MALBEC_OK;
-        if (run.block == 0 && !multi && !A.ckpt) rc = turns_blocks(n, A.n_steps, kTurnLaneBytes, turns, per_cu);
+        if (run.block == 0 && !A.ckpt) rc = turns_blocks(n, A.n_steps, kTurnLaneBytes, turns, per_cu);
         if (rc) return rc;
         if (A.ckpt)
             rc = multi ? launch_kernel<true, true, false>(A, T, block, 0, s)
                        : launch_kernel<false, true, false>(A, T, block, 0, s);
         else if (ham)
-            rc = multi ? launch_kernel<true, false, true>(A, T, block, 0, s)
+            rc = multi ? launch_kernel<true, false, true>(A, T, block, turns, s)
                        : launch_kernel<false, false, true>(A, T, block, turns, s);
         else
-            rc = multi ? launch_kernel<true, false, false>(A, T, block, 0, s)
+            rc = multi ? launch_kernel<true, false, false>(A, T, block, turns, s)
                        : launch_kernel<false, false, false>(A, T, block, turns, s);
         if (rc) return rc;
     }

@@ -481,3 +481,14 @@ def test_launch_in_turns_gives_the_bits_of_one_thread_per_lane(m, orc, formulati
         assert set(torch.unique(out[0][1]).tolist()) >= {0, 1, 2, 4}
         for x, y in zip(*out):
             assert torch.equal(x, y)
+    # a batch of several spacetimes, some lanes with an index that is none of them
+    sts = [(1.0, 0.9), (1.0, 0.0), (2.0, 1.3)]
+    sol = torch.arange(n, dtype=torch.int32, device="cuda") % 3
+    sol[::4001] = 7
+    out = []
+    for block in (0, 256):
+        s, a, b = state.clone(), status0.clone(), steps0.clone()
+        m.integrate(s, a, b, sts, h=0.02, n_steps=101, block=block, formulation=formulation, st_of_lane=sol)
+        out.append((s.view(torch.int64), a, b))
+    for x, y in zip(*out):
+        assert torch.equal(x, y)
