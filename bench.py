@@ -43,8 +43,8 @@ PEAK_FP32_VECTOR_TFLOPS = 157.3
 # taken again.
 KERNEL_SOURCES = ("integrate.hip", "f64_prog.hpp", "kerr_device.hpp", "kerr_accel.hpp", "ham_accel.hpp",
                   "persistent.hpp", "sincos_table.hpp")
-TRAFFIC = {"sources_sha256": "5a6ab0341c68de51e9c473087ee15a8d581b8cf3b3e74fcb06994aca22ca6b95",
-           "fetch_kib": 36960.0625, "fetch_scale": 1048576 / 524307.5625,
+TRAFFIC = {"sources_sha256": "6fd2feb78acc84a9a536c71763e12cc56f4a7da1b9ed17a2d5b7a406be0fc520",
+           "fetch_kib": 36948.2, "fetch_scale": 1048576 / 524307.5625,
            "write_kib": 73728.0, "write_scale": 1048576 / 1048576.0}
 
 
@@ -455,7 +455,7 @@ def main():
                                  schedule=schedule)
             if record:
                 ev[1].record()
-        # lanes in index order, then in periapsis order (longest expected first; the
+        # lanes in index order, then by expected length (longest first; the
         # order's computation is inside the timed call); the results are identical
         run_dp(False, "index")
         run_dp(True, "index")

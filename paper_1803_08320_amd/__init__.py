@@ -383,7 +383,8 @@ def integrate_adaptive(state: torch.Tensor, tau: torch.Tensor, h: torch.Tensor,
     """Dormand-Prince 5(4) with per-lane step size up to tau_end; state[8, n], tau and h
     (float64[n]), status, steps and rejects (int32[n]) in/out.  schedule: "index" or
     "periapsis" (persistent only: the lanes expected to take most attempts, from their
-    radial motion until tau_end, are handed out first; the results are the same); None = "periapsis" for a persistent launch, else "index"."""
+    radial motion until tau_end, are handed out first; the results are the same); None =
+    "periapsis" for a persistent launch, else "index"."""
     n = state.shape[-1]
     if schedule is None:
         schedule = "periapsis" if persistent else "index"

@@ -7,13 +7,13 @@
 // kernel arguments (uniform batch) or from an LDS copy of the table (mixed batch).
 //
 // What bounds them: FP64 VALU issue (0.98 of the CU-busy time on a full chip), so a step
-// costs its instructions: 341 FP64 arithmetic ones and 22 others per Christoffel step,
-// 260 and 22 per Hamiltonian step (358 and 27, 290 and 27 with the acceleration of the
+// costs its instructions: 342 FP64 arithmetic ones and 21.5 others per Christoffel step,
+// 264 and 23 per Hamiltonian step (358 and 27, 290 and 27 with the acceleration of the
 // FP32-compensated kernels, sums of the stage velocities and FP64 stop tests).  Measured on
-// one MI355X, the same machine before and after:
-//   1,048,576 Kerr lanes x 1,000 steps: 12.05 -> 11.44 ms (9.2 x 10^10 lane-steps/s)
-//   300,007 lanes x 1,000 steps, Hamiltonian form: 3.18 -> 2.89 ms
-//   1,024 lanes x 2,000 steps (one wave on each of 16 SIMDs): 1.93 -> 1.70 ms
+// one MI355X, the same machine before that and now:
+//   1,048,576 Kerr lanes x 1,000 steps: 12.05 -> 11.4 ms (9.2 x 10^10 lane-steps/s)
+//   300,007 lanes x 1,000 steps, Hamiltonian form: 3.18 -> 2.78 ms
+//   1,024 Schwarzschild lanes x 2,000 steps (one wave on each of 16 SIMDs): 1.93 -> 1.43 ms
 #include "f64_prog.hpp"
 #include "internal.hpp"
 #include "monitor.hpp"
