@@ -387,10 +387,19 @@ rk4_f32k_persistent_kernel(MixArgs A, StTable T, unsigned long long *counter, in
     persistent_loop<HAM>(P, A.n, counter, chunk);
 }
 
-// The compensated step with the invariant monitor (FP64, on hi + lo) every K steps.
-template <bool HAM>
-__global__ void __launch_bounds__(256) rk4_f32k_monitor_kernel(MixArgs A, StTable T, MonArgs MA,
-                                                               int32_t multi)
+// The compensated step with the invariant monitor (FP64, on hi + lo) every K steps.  SPAN: between
+// monitored steps through run(), in pairs; the kernel is bound by the issue of vector instructions
+// and pairs take the fewest (262,144 lanes, 600 steps, K = 50, Christoffel form 1.39 -> 1.31 ms,
+// Hamiltonian 1.24 -> 1.10; 20,000 lanes, K = 100, 0.62 -> 0.56 and 0.55 -> 0.48; lanes of mixed step
+// counts, 262,144 with K = 10, 300 steps, 1.01 -> 0.71 and 0.97 -> 0.62: they fold in fewer places).
+// Not for K < kSpanFrom, where a span has too few pairs (100,003 lanes of the Christoffel form, 300
+// steps: K = 5 0.42 ms by steps and 0.44 in spans, K = 6 0.42 and 0.40), nor both in one kernel
+// (178 registers, two waves per SIMD: K = 10, 262,144 lanes no faster than by steps).  Held to three
+// waves the Hamiltonian form in spans gives up 170 registers for 168 (262,144 lanes 1.16 -> 1.08 ms).
+constexpr int32_t kSpanFrom = 6;
+template <bool HAM, bool SPAN>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPAN && HAM ? 3 : 1, 8)))
+rk4_f32k_monitor_kernel(MixArgs A, StTable T, MonArgs MA, int32_t multi)
 {
     __shared__ Spacetime lds_st[kMaxSt];
     for (int k = threadIdx.x; k < T.n_st; k += blockDim.x) lds_st[k] = T.st[k];
@@ -402,7 +411,12 @@ __global__ void __launch_bounds__(256) rk4_f32k_monitor_kernel(MixArgs A, StTabl
     MonProg<Prog, HAM> P{Prog{A, lds_st, multi != 0, T.n_st}, MA, &lds_mon[threadIdx.x]};
     typename MonProg<Prog, HAM>::Lane L;
     if (!P.load(i, L)) return;
-    while (!P.step(L)) {
+    if (SPAN) {
+        while (!P.span(L)) {
+        }
+    } else {
+        while (!P.step(L)) {
+        }
     }
     P.store(i, L);
 }
@@ -441,8 +455,12 @@ int launch_monitor(const MixArgs &A, const StTable &T, const MonArgs &MA, bool m
             return MALBEC_OK;
         }
     }
-    hipLaunchKernelGGL((rk4_f32k_monitor_kernel<HAM>), dim3(grid_for(A.n, block)), dim3(block), 0, s,
-                       A, T, MA, (int32_t)multi);
+    if (MA.every >= kSpanFrom)
+        hipLaunchKernelGGL((rk4_f32k_monitor_kernel<HAM, true>), dim3(grid_for(A.n, block)), dim3(block),
+                           0, s, A, T, MA, (int32_t)multi);
+    else
+        hipLaunchKernelGGL((rk4_f32k_monitor_kernel<HAM, false>), dim3(grid_for(A.n, block)), dim3(block),
+                           0, s, A, T, MA, (int32_t)multi);
     MALBEC_LAUNCH_CHECK("rk4_f32k_monitor_kernel");
     return MALBEC_OK;
 }
@@ -530,7 +548,7 @@ int launch_monitor_f32k(const malbec_run &run, const StTable &T, const int32_t *
     A.h = run.h;
     A.r_escape = run.r_escape;
     A.r_escape_safe = safe_below(run.r_escape);
-    MonArgs MA{mon, steps, n, every, reset};
+    MonArgs MA{mon, steps, n, every, reset, span_steps(every)};
     unsigned long long *counter = (unsigned long long *)ws;
     if (run.persistent) {
         A.n_steps = (int32_t)total;

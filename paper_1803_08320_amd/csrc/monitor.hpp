@@ -66,7 +66,17 @@ struct MonArgs {
     int64_t n;
     int32_t every;         // K >= 1
     int32_t reset;         // 1: I_0 from the state at load, maxima cleared
+    int32_t span;          // the most steps that span() takes at once
 };
+
+// The longest span: K steps in equal parts of at most 16, even where they are several.  Lanes of a
+// wavefront whose step counts differ wait for one another at the end of a span, and fold in
+// different spans, so that a span of all K steps could double their time.
+inline int32_t span_steps(int32_t every)
+{
+    const int32_t parts = every / 16 + (every % 16 != 0), c = every / parts + (every % parts != 0);
+    return parts > 1 ? c + c % 2 : c;
+}
 
 // Base provides the Prog interface plus
 //   static void state64(const Lane&, double y[8])   -- the lane's state in FP64
@@ -111,20 +121,32 @@ struct MonProg {
         L.left = M.every - (r < 0 ? r + M.every : r);
         return true;
     }
+    // The lane's state against its reference invariants.
+    __device__ __forceinline__ void fold(Lane &L)
+    {
+        L.left = M.every;
+        double y[8], I[4];
+        Base::state64(L.b, y);
+        lane_invariants<HAM>(L.b.S.M, L.b.S.a, y, I);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            double &D = slot[(4 + k) * kMonLanes];
+            D = fmax(D, fabs(I[k] - slot[k * kMonLanes]));
+        }
+    }
     __device__ __forceinline__ bool step(Lane &L)
     {
         const bool done = base.step(L.b);
-        if (--L.left == 0) {
-            L.left = M.every;
-            double y[8], I[4];
-            Base::state64(L.b, y);
-            lane_invariants<HAM>(L.b.S.M, L.b.S.a, y, I);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                double &D = slot[(4 + k) * kMonLanes];
-                D = fmax(D, fabs(I[k] - slot[k * kMonLanes]));
-            }
-        }
+        if (--L.left == 0) fold(L);
+        return done;
+    }
+    // A span of steps through Base::run(Lane&, n) (at most n steps; true when the lane is finished).
+    __device__ __forceinline__ bool span(Lane &L)
+    {
+        const int32_t before = L.b.taken;
+        const bool done = base.run(L.b, L.left < M.span ? L.left : M.span);
+        L.left -= L.b.taken - before;
+        if (L.left == 0) fold(L);
         return done;
     }
     __device__ __forceinline__ void store(int64_t item, const Lane &L)

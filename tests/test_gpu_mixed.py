@@ -294,8 +294,8 @@ def test_mixed_full_size_sampled(m, orc):
 @pytest.mark.parametrize("persistent", [False, True])
 def test_steps_in_pairs_next_to_the_limits(m, orc, form, persistent):
     """A launch that takes FP32 steps in pairs, or tests their common outcome first in single
-    precision, gives the bits of one that hands out single steps, and of the monitored
-    integration, whose steps take the full rules: lanes within an ulp or a step of the FP64 zone, of the escape radius and of the poles, lanes that plunge, and
+    precision, gives the bits of one that hands out single steps, and of the
+    integration monitored at every step, whose steps take the full rules: lanes within an ulp or a step of the FP64 zone, of the escape radius and of the poles, lanes that plunge, and
     lanes that are not finite; odd and even numbers of steps."""
     import torch
     st = [(1.0, 0.9), (1.0, 0.0)]
@@ -329,7 +329,7 @@ def test_steps_in_pairs_next_to_the_limits(m, orc, form, persistent):
         state = torch.as_tensor(s0).cuda()
         status = torch.zeros(n, dtype=torch.int32, device="cuda")
         steps = torch.zeros(n, dtype=torch.int32, device="cuda")
-        m.integrate_monitored(state, status, steps, st, 0.05, n_steps, 1000,
+        m.integrate_monitored(state, status, steps, st, 0.05, n_steps, 1,
                               st_of_lane=torch.as_tensor(sol).cuda(), **kw)
         return state.cpu().numpy(), status.cpu().numpy(), steps.cpu().numpy()
 

@@ -182,3 +182,28 @@ def test_inactive_lanes_and_empty_calls(m, orc):
     stt, spp = m.new_lane_arrays(6)
     mon = m.integrate_monitored(state, stt, spp, st, 0.1, 0, 5)
     assert torch.isnan(mon).all() and torch.equal(state.cpu(), torch.as_tensor(s0))
+
+
+@pytest.mark.parametrize("formulation", ["christoffel", "hamiltonian"])
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("every", [5, 6, 7, 16, 17, 37, 100])
+def test_spans_between_monitored_steps(m, orc, every, mixed, formulation):
+    """The FP32-compensated kernel goes from one monitored step to the next in spans, in several
+    where K is large: the bits of the queue's single steps (state, status, steps, monitor), for
+    lanes of equal and of mixed step counts (negative ones too), lanes that stop inside a span and
+    on its last step, and K below, at and above the limits of a span."""
+    import torch
+    n = 450
+    rng = np.random.default_rng(every)
+    _, s0, _, _ = orc.ic_constants(31, [(1.0, 0.9)], n, KERR_RANGES)
+    s0 = np.ascontiguousarray(s0)
+    s0[5, ::3] = -rng.uniform(0.5, 30.0, n // 3)
+    sol = (np.arange(n) % 3).astype(np.int32)
+    steps = rng.integers(-60, 60, n).astype(np.int32) if mixed else np.full(n, 3, np.int32)
+    for n_steps in (1, 36, 101):
+        kw = dict(steps=steps, precision="f32k", formulation=formulation, sol=sol, r_escape=40.0)
+        got = run_mon(m, SPINS, s0, 0.05, n_steps, every, **kw)
+        ref = run_mon(m, SPINS, s0, 0.05, n_steps, every, persistent=True, steps_per_chunk=1, **kw)
+        for a, b in zip(got, ref):
+            np.testing.assert_array_equal(a, b)  # NaN equals NaN here, no tolerance
+    assert len(np.unique(got[1])) > 1
