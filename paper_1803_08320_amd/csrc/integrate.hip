@@ -14,6 +14,7 @@
 //   1,048,576 Kerr lanes x 1,000 steps: 12.05 -> 11.4 ms (9.2 x 10^10 lane-steps/s)
 //   300,007 lanes x 1,000 steps, Hamiltonian form: 3.18 -> 2.78 ms
 //   1,024 Schwarzschild lanes x 2,000 steps (one wave on each of 16 SIMDs): 1.93 -> 1.43 ms
+#include "checkpoint.hpp"
 #include "f64_prog.hpp"
 #include "internal.hpp"
 #include "monitor.hpp"
@@ -66,13 +67,9 @@ __global__ void __launch_bounds__(256) rk4_f64_kernel(IntArgs A, StTable T)
 #pragma unroll
     for (int k = 0; k < 8; ++k) y[k] = A.state[k * A.n + i];
     const HamConst<double> P = ham_const(S.a, y[4], y[7]);
-    int32_t taken = 0;
-    int32_t next_slot = 0;
-    if (CKPT) next_slot = (A.k0 + A.ck_every - 1) / A.ck_every;  // first slot at or after k0
-
     if (!CKPT && st == kActive) {
         // a launch always has n_steps >= 1 (the launcher makes none for a call of zero steps)
-        taken = run_steps<HAM, ZERO_A>(S, P, A.h, A.r_escape, A.n_steps, y, st);
+        const int32_t taken = run_steps<HAM, ZERO_A>(S, P, A.h, A.r_escape, A.n_steps, y, st);
         // the lane's index rebuilt from wave-uniform values and its position in the
         // wavefront: no per-lane address stays live across the loop
         const int64_t ie = (int64_t)blockIdx.x * blockDim.x + wave0 +
@@ -81,30 +78,22 @@ __global__ void __launch_bounds__(256) rk4_f64_kernel(IntArgs A, StTable T)
         for (int k = 0; k < 8; ++k) A.state[k * A.n + ie] = y[k];
         A.status[ie] = st;
         A.steps[ie] += taken;
-    } else if (st == kActive) {
-        // from checkpoint to checkpoint
-        while (taken < A.n_steps && st == kActive) {
-            const int32_t k = A.k0 + taken;
-            if (k == next_slot * A.ck_every) {
-                put_slot(A, i, next_slot, y);
-                ++next_slot;
-            }
-            const int32_t to_slot = next_slot * A.ck_every - k, left = A.n_steps - taken;
-            taken += run_steps<HAM>(S, P, A.h, A.r_escape, to_slot < left ? to_slot : left, y, st);
-        }
+    } else if (CKPT) {
+        const bool was_active = st == kActive;
+        const int32_t taken = run_checkpointed(
+            A.k0, A.n_steps, A.ck_every, A.ck_last, was_active,
+            [&](int32_t m, bool &active) {
+                const int32_t ks = run_steps<HAM>(S, P, A.h, A.r_escape, m, y, st);
+                active = st == kActive;
+                return ks;
+            },
+            [&](int32_t slot) { put_slot(A, i, slot, y); });
+        if (was_active) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) A.state[k * A.n + i] = y[k];
-        A.status[i] = st;
-        A.steps[i] += taken;
-    }
-    if (CKPT) {
-        // slots up to the end of this launch (inclusive of the call's last slot when
-        // this launch ends the call) repeat the current state for stopped lanes and
-        // receive the end state otherwise
-        const int32_t end = A.k0 + A.n_steps;
-        int32_t last = end / A.ck_every;
-        if (last * A.ck_every == end && last != A.ck_last) --last;  // next launch writes it
-        for (int32_t s = next_slot; s <= last; ++s) put_slot(A, i, s, y);
+            for (int k = 0; k < 8; ++k) A.state[k * A.n + i] = y[k];
+            A.status[i] = st;
+            A.steps[i] += taken;
+        }
     }
 }
 
