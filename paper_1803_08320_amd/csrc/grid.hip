@@ -28,6 +28,7 @@
 // wavefront (one load per such lane instead of 40 under its mask) was 4 % slower: the
 // exchange through LDS lengthens the wait.
 #include "internal.hpp"
+#include "turns.hpp"
 
 namespace malbec {
 
@@ -310,8 +311,6 @@ rk4_grid_kernel(GridArgs A)
 
 // A batch that fills the chip unevenly, in turns (rk4_f64_turns_kernel in integrate.hip).  The stencils
 // take the LDS, so the lanes that wait are parked where they came from, in the state arrays (L2).
-// The threads of a turn are a run of the sequence 0, 1, .. m - 1, 0, 1, ..: lane j has had
-// position / m turns, each of q steps while it was active.
 template <typename Node>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 rk4_grid_turns_kernel(GridArgs A, int32_t share, int32_t q)
@@ -320,13 +319,13 @@ rk4_grid_turns_kernel(GridArgs A, int32_t share, int32_t q)
     const int64_t base = (int64_t)blockIdx.x * share;
     const int64_t rest = A.n - base;
     const int32_t m = rest < share ? (int32_t)rest : share;  // lanes of this block (may be <= 0)
-    const int32_t runs = (A.n_steps + q - 1) / q;
-    const int64_t turns = m >= 256 ? ((int64_t)runs * m + 255) / 256 : runs;
+    const int64_t turns = turns_of_block(A.n_steps, q, m);
     Stencil C;
     C.lds = &lds_stencil[(threadIdx.x / 64u) * (kLdsChunks * 64) + threadIdx.x % 64u];
-    int32_t j = (int32_t)threadIdx.x, gone = 0;  // the lane, and the steps it has had if active
+    int32_t j = (int32_t)threadIdx.x, had = 0;  // the lane, and the turns it has had
     for (int64_t turn = 0; turn < turns; ++turn) {
-        if (j < m && gone < A.n_steps) {
+        const int32_t steps = steps_of_turn(A.n_steps, q, had);
+        if (j < m && steps > 0) {
             const int64_t i = base + j;
             int32_t st = A.status[i];
             if (st == kActive) {
@@ -335,8 +334,7 @@ rk4_grid_turns_kernel(GridArgs A, int32_t share, int32_t q)
                 for (int k = 0; k < 8; ++k) y[k] = A.state[k * A.n + i];
                 const HamConst<double> P{y[4], y[7], 0.0, 0.0};
                 C.ci = C.cj = -1;
-                const int32_t left = A.n_steps - gone;
-                const int32_t taken = grid_steps<Node>(A, P, C, q < left ? q : left, y, st);
+                const int32_t taken = grid_steps<Node>(A, P, C, steps, y, st);
                 const int64_t ie = opaque(i);
 #pragma unroll
                 for (int k = 0; k < 8; ++k) A.state[k * A.n + ie] = y[k];
@@ -344,15 +342,7 @@ rk4_grid_turns_kernel(GridArgs A, int32_t share, int32_t q)
                 A.steps[ie] += taken;
             }
         }
-        if (m < 256) {
-            gone += q;
-        } else {
-            j += 256;
-            if (j >= m) {
-                j -= m;
-                gone += q;
-            }
-        }
+        next_turn(m, j, had);
         __syncthreads();
     }
 }

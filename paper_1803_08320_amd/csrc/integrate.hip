@@ -18,6 +18,7 @@
 #include "f64_prog.hpp"
 #include "internal.hpp"
 #include "monitor.hpp"
+#include "turns.hpp"
 
 namespace malbec {
 
@@ -133,9 +134,7 @@ __global__ void __launch_bounds__(256) rk4_f64_turns_kernel(IntArgs A, StTable T
     __syncthreads();
     Spacetime S = T.st[0];
     if (UNIT_M) S.M = 1.0;
-    const int32_t runs = (A.n_steps + q - 1) / q;
-    // m >= 256: the turns tile the lanes in order; fewer lanes: each thread keeps its own
-    const int64_t turns = m >= 256 ? ((int64_t)runs * m + 255) / 256 : runs;
+    const int64_t turns = turns_of_block(A.n_steps, q, m);
     int32_t j = t;
     for (int64_t turn = 0; turn < turns; ++turn) {
         if (j < m && lane_st[j] == kActive && lane_taken[j] < A.n_steps) {

@@ -11,6 +11,7 @@
 // unevenly, in turns.
 #include "f64_prog.hpp"
 #include "internal.hpp"
+#include "turns.hpp"
 
 namespace malbec {
 
@@ -156,8 +157,7 @@ rk4_record_turns_kernel(RecArgs A, StTable T, int32_t share, int32_t per)
     }
     __syncthreads();
     const Spacetime S = T.st[0];
-    const int32_t runs = (A.n_rec + per - 1) / per;
-    const int64_t turns = m >= 256 ? ((int64_t)runs * m + 255) / 256 : runs;
+    const int64_t turns = turns_of_block(A.n_rec, per, m);
     int32_t j = t;
     for (int64_t turn = 0; turn < turns; ++turn) {
         if (j < m && lane_rec[j] < A.n_rec) {
