@@ -319,16 +319,18 @@ rk4_grid_turns_kernel(GridArgs A, int32_t share, int32_t q)
     const int64_t base = (int64_t)blockIdx.x * share;
     const int64_t rest = A.n - base;
     const int32_t m = rest < share ? (int32_t)rest : share;  // lanes of this block (may be <= 0)
-    const int64_t turns = turns_of_block(A.n_steps, q, m);
+    const int32_t turns = turns_of_block(A.n_steps, q, m);
     Stencil C;
     C.lds = &lds_stencil[(threadIdx.x / 64u) * (kLdsChunks * 64) + threadIdx.x % 64u];
+    bool worked = false;  // a lane of this thread stepped since the last look
     int32_t j = (int32_t)threadIdx.x, had = 0;  // the lane, and the turns it has had
-    for (int64_t turn = 0; turn < turns; ++turn) {
+    for (int32_t turn = 0; turn < turns; ++turn) {
         const int32_t steps = steps_of_turn(A.n_steps, q, had);
         if (j < m && steps > 0) {
             const int64_t i = base + j;
             int32_t st = A.status[i];
             if (st == kActive) {
+                worked = true;
                 double y[8];
 #pragma unroll
                 for (int k = 0; k < 8; ++k) y[k] = A.state[k * A.n + i];
@@ -344,6 +346,18 @@ rk4_grid_turns_kernel(GridArgs A, int32_t share, int32_t q)
         }
         next_turn(m, j, had);
         __syncthreads();
+        if (look_after(turn)) {
+            // the threads' answers go through the stencils' LDS (free between turns; another word of LDS
+            // would leave room for one block per CU instead of two)
+            if (threadIdx.x == 0) lds_stencil[0][0] = 0.0;
+            __syncthreads();
+            if (worked) lds_stencil[0][0] = 1.0;
+            __syncthreads();
+            const bool any = lds_stencil[0][0] != 0.0;
+            __syncthreads();
+            if (!any) break;
+            worked = false;
+        }
     }
 }
 

@@ -105,18 +105,21 @@ __global__ void __launch_bounds__(256) rk4_f64_kernel(IntArgs A, StTable T)
 // its steps after (steps / q) share / 256 turns and no SIMD waits.  Between its turns a lane is
 // parked in LDS (72 B).  The rule for taking this launch (turns_blocks) and its measurements are in
 // api.hip.
+static_assert(160 * 1024 / kTurnLaneBytes < kMaxShare, "the lanes parked in a CU's LDS");
 template <bool MULTI, bool HAM, bool UNIT_M, bool ZERO_A>
 __global__ void __launch_bounds__(256) rk4_f64_turns_kernel(IntArgs A, StTable T, int32_t share, int32_t q)
 {
     __shared__ Spacetime lds_st[MULTI ? kMaxSt : 1];
     if (MULTI)
         for (int k = threadIdx.x; k < T.n_st; k += blockDim.x) lds_st[k] = T.st[k];
+    __shared__ int32_t worked;        // the last turn in which a lane stepped
     extern __shared__ double park[];  // [8][share], then status and steps taken
     int32_t *lane_st = (int32_t *)(park + 8 * share), *lane_taken = lane_st + share;
     const int64_t base = (int64_t)blockIdx.x * share;
     const int64_t rest = A.n - base;
     const int32_t m = rest < share ? (int32_t)rest : share;  // lanes of this block (may be <= 0)
     const int32_t t = (int32_t)threadIdx.x;
+    if (t == 0) worked = 0;
     for (int32_t j = t; j < m; j += 256) {
         int32_t st = A.status[base + j];
         if (MULTI) {
@@ -134,9 +137,9 @@ __global__ void __launch_bounds__(256) rk4_f64_turns_kernel(IntArgs A, StTable T
     __syncthreads();
     Spacetime S = T.st[0];
     if (UNIT_M) S.M = 1.0;
-    const int64_t turns = turns_of_block(A.n_steps, q, m);
+    const int32_t turns = turns_of_block(A.n_steps, q, m);
     int32_t j = t;
-    for (int64_t turn = 0; turn < turns; ++turn) {
+    for (int32_t turn = 0; turn < turns; ++turn) {
         if (j < m && lane_st[j] == kActive && lane_taken[j] < A.n_steps) {
             const int32_t taken = lane_taken[j], left = A.n_steps - taken;
             int32_t st = kActive;
@@ -149,12 +152,15 @@ __global__ void __launch_bounds__(256) rk4_f64_turns_kernel(IntArgs A, StTable T
             lane_st[j] = st;
 #pragma unroll
             for (int k = 0; k < 8; ++k) park[k * share + j] = y[k];
+            worked = turn;
         }
         if (m >= 256) {
             j += 256;
             if (j >= m) j -= m;
         }
         __syncthreads();
+        // a thread that is ahead may have written a later turn: only where this one goes on, too
+        if (look_after(turn) && worked <= turn - kIdleTurns) break;
     }
     for (int32_t i = t; i < m; i += 256) {
         const int32_t taken = lane_taken[i];

@@ -157,9 +157,9 @@ rk4_record_turns_kernel(RecArgs A, StTable T, int32_t share, int32_t per)
     }
     __syncthreads();
     const Spacetime S = T.st[0];
-    const int64_t turns = turns_of_block(A.n_rec, per, m);
+    const int32_t turns = turns_of_block(A.n_rec, per, m);
     int32_t j = t;
-    for (int64_t turn = 0; turn < turns; ++turn) {
+    for (int32_t turn = 0; turn < turns; ++turn) {
         if (j < m && lane_rec[j] < A.n_rec) {
             int32_t st = lane_st[j], steps = lane_steps[j], rec = lane_rec[j];
             const int32_t end = A.n_rec - rec < per ? A.n_rec : rec + per;

@@ -10,11 +10,12 @@
 
 namespace malbec {
 
-// Turns of the block until every lane has had n_steps steps.
-MALBEC_HD inline int64_t turns_of_block(int32_t n_steps, int32_t q, int32_t m)
+// Turns of the block until every lane has had n_steps steps (at most
+// 2^27 runs of q steps, and m < 4096, below 2^31 turns).
+MALBEC_HD inline int32_t turns_of_block(int32_t n_steps, int32_t q, int32_t m)
 {
     const int32_t runs = n_steps / q + (n_steps % q != 0);
-    return m >= 256 ? ((int64_t)runs * m + 255) / 256 : runs;
+    return m >= 256 ? (int32_t)(((int64_t)runs * m + 255) / 256) : runs;
 }
 
 // The steps of a lane's next turn after it has had `had` whole ones, 0 when it has had all.
@@ -37,5 +38,12 @@ MALBEC_HD inline void next_turn(int32_t m, int32_t &j, int32_t &had)
         ++had;
     }
 }
+
+// A block whose lanes have all stopped leaves its remaining turns out, as one thread per lane would (a
+// run "until every lane stops" has a step count far beyond its longest lane): it looks every kIdleTurns
+// turns whether one of its threads had a lane that stepped in them, in which every lane has had its turn.
+constexpr int32_t kIdleTurns = 16;
+constexpr int32_t kMaxShare = kIdleTurns * 256;  // the lanes of a block are fewer
+MALBEC_HD inline bool look_after(int32_t turn) { return turn % kIdleTurns == kIdleTurns - 1; }
 
 }  // namespace malbec
