@@ -27,6 +27,7 @@
 // stay in their cells or not).  Gathering for the few lanes that change cell by the whole
 // wavefront (one load per such lane instead of 40 under its mask) was 4 % slower: the
 // exchange through LDS lengthens the wait.
+#include "grid_weights.hpp"
 #include "internal.hpp"
 #include "turns.hpp"
 
@@ -42,31 +43,11 @@ struct GridArgs {
     const void *nodes;  // Node[nr * nth * 5], Node = double or float
     int32_t nr, nth;
     double r0, idr, th0, idth;   // inverse spacings
+    double idr6, idth6;          // a sixth of them
     double rlo, rhi, tlo, thi;   // interior (stencils and stage points stay inside)
     double r_stop, r_escape, h;
     int32_t n_steps;
 };
-
-// Lagrange basis on the nodes -1, 0, 1, 2 at u, and its derivative:
-//   w = {-u (u-1)(u-2)/6, (u+1)(u-1)(u-2)/2, -(u+1) u (u-2)/2, (u+1) u (u-1)/6}.
-// One inner weight of each set is formed as what the other three leave of the sum (1 and
-// 0): the rounding of the sum is what the large node values (gamma_thth ~ r^2) carry into
-// the derivatives.  Measured over u in [0, 1): the sums are off by 3.6e-17 and 6.1e-17
-// rms, against 5.3e-17 and 8.7e-17 with every weight from its own product.
-__device__ __forceinline__ void lagrange4(double u, double w[4], double dw[4])
-{
-    const double p = fma(u, u, -u);    // u (u - 1)
-    const double q = p - 2.0;          // (u + 1)(u - 2)
-    w[0] = p * fma(u, -1.0 / 6.0, 1.0 / 3.0);
-    w[2] = q * (-0.5 * u);
-    w[3] = p * fma(u, 1.0 / 6.0, 1.0 / 6.0);
-    w[1] = (1.0 - w[2]) - (w[0] + w[3]);
-    const double uu = u * u;
-    dw[0] = fma(uu, -0.5, u - 1.0 / 3.0);
-    dw[2] = fma(uu, -1.5, u + 1.0);
-    dw[3] = fma(uu, 0.5, -1.0 / 6.0);
-    dw[1] = -(dw[0] + dw[3]) - dw[2];
-}
 
 // Cell index of x on a grid of n nodes (the stencil starts one node before) and the
 // offset u in it.  The index is clamped to [1, n - 3] as an integer (the conversion
@@ -135,7 +116,7 @@ __device__ __forceinline__ void stencil_load(const GridArgs &A, int32_t i, int32
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// F, dF/du_r and dF/du_theta (u: the offset in cells) of the five functions at
+// F, 6 dF/du_r and 6 dF/du_theta (u: the offset in cells) of the five functions at
 // (r, theta).  Function by function: the theta contraction of its four rows, value and
 // derivative, then the r contraction (44 fma).
 template <typename Node>
@@ -218,8 +199,8 @@ __device__ __forceinline__ void grid_ham(const GridArgs &A, const HamConst<doubl
         const double kin = fma(rr, D[2], fma(hh, D[3], w2s2 * D[4]));
         return fma(0.5, kin, fma(c0, D[0], c1 * D[1]));
     };
-    dpr = A.idr * force(Fr);
-    dpth = fma(A.idth, force(Ft), (w2 * sc) * F[4]);
+    dpr = A.idr6 * force(Fr);
+    dpth = fma(A.idth6, force(Ft), (w2 * sc) * F[4]);
 }
 
 // Up to n_steps steps of an active lane from y, which receives its state after them; returns
@@ -446,6 +427,8 @@ int launch_integrate_grid(const malbec_run &run, const malbec_grid &g, int64_t n
     A.idr = 1.0 / g.dr;
     A.th0 = g.th0;
     A.idth = 1.0 / g.dth;
+    A.idr6 = (double)(1.0L / (6.0L * g.dr));
+    A.idth6 = (double)(1.0L / (6.0L * g.dth));
     A.rlo = g.r0 + g.dr;
     A.rhi = g.r0 + (double)(g.nr - 2) * g.dr;
     A.tlo = g.th0 + g.dth;
