@@ -49,13 +49,22 @@ struct GridArgs {
     int32_t n_steps;
 };
 
+// x truncated to an integer for every double: the instruction saturates and takes a NaN to 0, where
+// the language leaves such conversions undefined.
+__device__ __forceinline__ int32_t truncated(double x)
+{
+    int32_t i;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(i) : "v"(x));
+    return i;
+}
+
 // Cell index of x on a grid of n nodes (the stencil starts one node before) and the
-// offset u in it.  The index is clamped to [1, n - 3] as an integer (the conversion
-// saturates and takes NaN to 0), so every access stays inside the grid.
+// offset u in it.  The index is clamped to [1, n - 3] as an integer, so every access stays
+// inside the grid, also for stage points off the grid and for NaN.
 __device__ __forceinline__ int32_t cell(double x, double x0, double ih, int32_t n, double &u)
 {
     const double q = (x - x0) * ih;
-    const int32_t i = min(max((int32_t)q, 1), n - 3);
+    const int32_t i = min(max(truncated(q), 1), n - 3);
     u = q - (double)i;
     return i;
 }

@@ -63,3 +63,38 @@ def test_values_and_derivatives_have_no_bias(host, f, x0, dx):
         own_rms = float(np.sqrt(((((own.astype(LD) * F).sum(0) - want) / want) ** 2).mean()))
         assert abs(float(err.mean())) <= 5 * rms / np.sqrt(n)
         assert rms <= own_rms
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("f32", [False, True])
+def test_stage_points_anywhere(orc, f32):
+    """Momenta that carry the stage points off the grid by any distance, to infinity and to NaN: every
+    gather stays inside the grid, and the lanes end as the oracle's, after the same number of steps (as
+    HORIZON or as NONFINITE where the square of the momentum overflows, which the oracle forms in
+    another order)."""
+    import torch
+
+    import paper_1803_08320_amd as m
+    G = orc.grid_kerr(1.0, 0.6, 33, 17, 4.0, 0.5, 0.5, 0.13)
+    nodes = G.nodes.astype(np.float32) if f32 else G.nodes
+    G = orc.Grid(nodes.astype(np.float64), G.r0, G.dr, G.th0, G.dth)
+    g = m.Grid(torch.as_tensor(nodes).cuda(), G.r0, G.dr, G.th0, G.dth, 4.6)
+    vals = [s * v for v in (1.0, 1e2, 1e9, 3e9, 1e10, 1e20, 1e100, 1e154, 1e300) for s in (1, -1)]
+    vals += [np.inf, -np.inf, np.nan]
+    z = []
+    for c in (4, 5, 6, 7):
+        for v in vals:
+            for r, th in ((4.7, 0.7), (9.0, 1.5), (18.0, 2.4)):
+                y = np.array([0.0, r, th, 0.0, -0.95, 0.05, 0.3, 2.0])
+                y[c] = v
+                z.append(y)
+    z = np.array(z).T.copy()
+    state = torch.as_tensor(z).cuda()
+    status, steps = m.new_lane_arrays(z.shape[1])
+    m.integrate_grid(state, status, steps, g, 0.05, 20, 18.5)
+    ref = orc.integrate_grid(G, z, 0.05, 20, r_stop=4.6, r_escape=18.5)
+    got, huge = status.cpu().numpy(), ~(np.abs(z[4:]).max(axis=0) < 1e154)
+    assert np.array_equal(got[~huge], ref[1][~huge])
+    assert np.array_equal(got[huge] == 0, ref[1][huge] == 0)
+    assert np.array_equal(steps.cpu().numpy(), ref[2])
+    assert set(np.unique(ref[1])) >= {0, 1, 4}
