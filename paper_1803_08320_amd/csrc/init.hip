@@ -170,18 +170,31 @@ __device__ __forceinline__ Draw draw_attempt(const malbec_ic_spec &P, uint64_t l
     return D;
 }
 
-// R(r) >= 0 and Theta(theta) >= 0, the latter multiplied by sin^2 theta (no division).
-// The reduction of sincos_any holds for |theta| < 1e6; big_theta: a range beyond it.
+// R(r) >= 0 and Theta(theta) >= 0.  The sign of Theta comes from Theta sin^2 theta (no division) where that is
+// clear of its own rounding and of that of sincos_any (whose reduction holds for |theta| < 1e6 and whose
+// sin or cos loses relative accuracy next to a multiple of pi/2); elsewhere from the expression that the
+// lane's state is formed with, so that a draw on the boundary is decided as its state will have it.
+// big_theta: a range beyond sincos_any.
 __device__ __forceinline__ bool admissible(const malbec_ic_spec &P, double M, double a, const Draw &D,
                                            bool big_theta)
 {
-    double s, c;
-    if (big_theta) sincos(D.th, &s, &c);
-    else sincos_any(D.th, s, c);
-    const double s2 = s * s, c2 = c * c;
     const double R = radial_potential(M, a, D.E, D.L, D.Q, P.mu2, D.r);
-    const double T = D.Q * s2 - c2 * (a * a * (P.mu2 - D.E * D.E) * s2 + D.L * D.L);
-    return R >= 0.0 && T >= 0.0 && s2 > 0.0;
+    if (!(R >= 0.0)) return false;
+    double s, c;
+    bool ok = false, close = true;
+    if (!big_theta) {
+        sincos_any(D.th, s, c);
+        const double s2 = s * s, c2 = c * c, LL = D.L * D.L;
+        const double Qs = D.Q * s2, k = a * a * (P.mu2 - D.E * D.E) * s2;
+        const double T = Qs - c2 * (k + LL);
+        ok = T > 0.0;
+        close = !(fabs(T) > 1e-12 * (fabs(Qs) + c2 * (fabs(k) + LL))) || !(fmin(s2, c2) > 1e-10);
+    }
+    if (close) {
+        sincos(D.th, &s, &c);
+        ok = polar_potential(a, D.E, D.L, D.Q, P.mu2, s, c) >= 0.0;
+    }
+    return ok;
 }
 
 // A lane takes as many attempts as it needs (20 on the average for the benchmark's ranges,
