@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include "internal.hpp"
+#include "turns.hpp"
 
 namespace malbec {
 
@@ -39,36 +40,14 @@ int persistent_grid(const void *kernel, int block, int64_t n_items, int &grid)
     return MALBEC_OK;
 }
 
-// The blocks of a launch in turns (rk4_f64_turns_kernel), 0 where one thread per lane is the better
-// launch.  With n / (256 lanes per CU) = w + f, w whole, one thread per lane takes the time of w + 1
-// blocks on every CU, in turns w blocks per CU (four at most) share the lanes.  FP64 kernels, 1,000 steps on
-// one MI355X, one thread per lane and in turns, ms (Christoffel; Hamiltonian form):
-//   w + f   1.1            1.5            1.65           2.1            2.6            3.1
-//         1.47 1.02      1.48 1.34      1.48 1.48      2.16 1.64      2.18 2.00      2.89 2.38
-//         1.19 0.85      1.21 1.13      1.21 1.25      1.71 1.36      1.73 1.62      2.26 1.91
-//   w + f   3.6            4.0 (263,454)  4.6            5.3            6.5            8.1
-//         2.86 2.73      3.61 2.99      3.58 3.41      4.29 3.92      5.03 4.84      6.50 6.06
-//         2.27 2.16      2.85 2.39      2.82 2.73      3.38 3.14      3.96 3.91      5.13 4.89
-// So in turns for f up to 0.55 with one block per CU and 0.6 with more (f = 0.8: even, or 2 % slower);
-// a batch of 16 spacetimes gains as much.  A turn costs about 0.4 us besides its
-// steps, and the last one is partly idle: at 100 steps the gain at w + f = 1.5 and 4.6 is still 8 and
-// 2 %, at 64 steps it is within +-2 %, at 32 none, so from 100 steps on.  The parked lanes of four blocks
-// have to fit a CU's LDS, which ends it at w + f = 8.9.
-int turns_blocks(int64_t n, int64_t n_steps, int lane_bytes, int32_t &blocks, int32_t &per_cu)
+// The blocks of a launch in turns (blocks = 0: one thread per lane is the better launch) by the rule of turns.hpp.
+int turns_blocks(int64_t n, int64_t n_steps, int32_t &blocks, int32_t &per_cu)
 {
-    blocks = per_cu = 0;
-    if (n_steps < 100) return MALBEC_OK;
     int dev = 0, n_cu = 0;
     MALBEC_HIP_CHECK(hipGetDevice(&dev));
     MALBEC_HIP_CHECK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-    const int64_t level = (int64_t)n_cu * 256;
-    const int64_t w = n / level;
-    if (w < 1 || n == w * level || (double)(n - w * level) > (w == 1 ? 0.55 : 0.6) * (double)level) return MALBEC_OK;
-    const int64_t k = w < 4 ? w : 4, g = k * n_cu;
-    const int64_t share = (n + g - 1) / g;
-    if (k * share * lane_bytes > 160 * 1024) return MALBEC_OK;
-    per_cu = (int32_t)k;
-    blocks = (int32_t)g;
+    per_cu = turns_per_cu(n, n_cu, n_steps);
+    blocks = per_cu * n_cu;
     return MALBEC_OK;
 }
 

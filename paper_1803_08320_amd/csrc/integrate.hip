@@ -102,10 +102,9 @@ __global__ void __launch_bounds__(256) rk4_f64_kernel(IntArgs A, StTable T)
 // SIMDs, so that half of these run two, and the other half wait for them.  Here a whole number of
 // blocks per CU takes `share` >= 256 consecutive lanes each and advances 256 of them at a time by q
 // steps, in turns: turn t runs the lanes t 256 .. t 256 + 255 modulo the share, so that every lane has
-// its steps after (steps / q) share / 256 turns and no SIMD waits.  Between its turns a lane is
+// its steps after (steps / q) share / 256 turns, at the same time on every SIMD.  Between its turns a lane is
 // parked in LDS (72 B).  The rule for taking this launch (turns_blocks) and its measurements are in
 // api.hip.
-static_assert(160 * 1024 / kTurnLaneBytes < kMaxShare, "the lanes parked in a CU's LDS");
 template <bool MULTI, bool HAM, bool UNIT_M, bool ZERO_A>
 __global__ void __launch_bounds__(256) rk4_f64_turns_kernel(IntArgs A, StTable T, int32_t share, int32_t q)
 {
@@ -311,7 +310,7 @@ int launch_integrate_f64(const malbec_run &run, const StTable &T, const int32_t 
         A.n_steps = (int32_t)((total - k0) < chunk ? (total - k0) : chunk);
         int32_t turns = 0, per_cu = 0;
         int rc = MALBEC_OK;
-        if (run.block == 0 && !A.ckpt) rc = turns_blocks(n, A.n_steps, kTurnLaneBytes, turns, per_cu);
+        if (run.block == 0 && !A.ckpt) rc = turns_blocks(n, A.n_steps, turns, per_cu);
         if (rc) return rc;
         if (A.ckpt)
             rc = multi ? launch_kernel<true, true, false>(A, T, block, 0, s)

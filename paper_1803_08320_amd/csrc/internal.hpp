@@ -70,7 +70,7 @@ inline bool queue_is_idle(int64_t n, int grid, int block) { return (int64_t)grid
 // Launches in turns: LDS per lane, steps per turn, and the rule (blocks = 0: not in turns).
 constexpr int kTurnLaneBytes = 72;
 constexpr int32_t kTurnSteps = 16;
-int turns_blocks(int64_t n, int64_t n_steps, int lane_bytes, int32_t &blocks, int32_t &per_cu);
+int turns_blocks(int64_t n, int64_t n_steps, int32_t &blocks, int32_t &per_cu);
 int launch_camera(const malbec_camera &cam, double r_stop, double disk_r_in, int32_t *status,
                   int32_t *steps, double *hit, double *final_state, void *ws, hipStream_t s);
 int launch_adjoint(const malbec_run &run, const StTable &T, const int32_t *st_of_lane, int64_t n,

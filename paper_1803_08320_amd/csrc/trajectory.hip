@@ -136,7 +136,8 @@ __global__ void __launch_bounds__(256) rk4_record_kernel(RecArgs A, StTable T)
 // 1.45, 150,000 lanes 2.29 and 1.93, Hamiltonian form 1.27 and 0.87, 1.28 and 1.21, 1.84 and 1.57.
 // Turns that end within an interval cost a second, short loop: 100,003 lanes 1.73 ms with 16 steps.
 // THREE: at least three blocks per CU, for which the Christoffel form (177 registers) and the
-// Hamiltonian one have to be held to three waves per SIMD; with fewer blocks that costs them 5 %.
+// Hamiltonian one have to be held to three waves per SIMD; with fewer blocks that costs them 5 %.  Of
+// four blocks per CU the fourth then follows as the others end (w + f = 4.1: 1.97 ms, with three 2.02).
 template <bool HAM, bool THREE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(THREE ? 3 : 1, 8)))
 rk4_record_turns_kernel(RecArgs A, StTable T, int32_t share, int32_t per)
@@ -219,7 +220,7 @@ int launch_integrate_record(const malbec_run &run, const StTable &T, const int32
     if (run.block == 0 && !multi && record_every >= 8 && A.n_rec >= 6 * per) {
         constexpr int kLaneBytes = kTurnLaneBytes + 4;
         int32_t turns = 0, per_cu = 0;
-        const int rc = turns_blocks(n, run.n_steps, kLaneBytes, turns, per_cu);
+        const int rc = turns_blocks(n, run.n_steps, turns, per_cu);
         if (rc) return rc;
         if (turns > 0) {
             const int32_t share = (int32_t)((n + turns - 1) / turns);

@@ -14,6 +14,7 @@ MAX = 2**31 - 1
 SRC = r"""
 #include <vector>
 #include "turns.hpp"
+extern "C" int32_t per_cu(int64_t n, int64_t steps) { return malbec::turns_per_cu(n, 256, steps); }
 extern "C" int32_t turn_count(int32_t n_steps, int32_t q, int32_t m) { return malbec::turns_of_block(n_steps, q, m); }
 extern "C" int32_t steps_after(int32_t n_steps, int32_t q, int32_t had) { return malbec::steps_of_turn(n_steps, q, had); }
 // The turns of a block, lane k stopping after stop(k) = k * stride steps (stride < 0: never).  0 when
@@ -52,6 +53,7 @@ def host(tmp_path_factory):
                     "-fsanitize-undefined-trap-on-error", "-I",
                     os.path.join(ROOT, "paper_1803_08320_amd", "csrc"), str(src), "-o", str(so)], check=True)
     lib = C.CDLL(str(so))
+    lib.per_cu.argtypes = [C.c_int64, C.c_int64]
     return lib
 
 
@@ -75,6 +77,27 @@ def test_turns_of_the_longest_calls(host, q, m):
         assert host.steps_after(n_steps, q, runs - 2) == q
         assert 0 < host.steps_after(n_steps, q, runs - 1) == n_steps - (runs - 1) * q
         assert host.steps_after(n_steps, q, runs) == host.steps_after(n_steps, q, runs + 1) == 0
+
+
+@pytest.mark.parametrize("w,most,blocks", [(1, 0.55, 1), (2, 0.6, 2), (3, 0.6, 3), (4, 0.6, 4), (5, 0.6, 4),
+                                           (6, 0.45, 4), (7, 0.3, 4), (8, 0.3, 4)])
+def test_rule_at_its_limits(host, w, most, blocks):
+    """A whole number of levels and the lanes beyond the limit take one thread per lane, between them the
+    launch is in turns, from 100 steps on; the blocks that are resident fit the LDS."""
+    level = 256 * 256
+    last = w * level + int(most * level)
+    assert host.per_cu(w * level, 1000) == 0
+    assert host.per_cu(w * level + 1, 100) == blocks
+    assert host.per_cu(last, 2**31 - 1) == blocks
+    assert host.per_cu(last + 1, 1000) == 0
+    assert host.per_cu(w * level + 1, 99) == 0
+    share = -(-last // (256 * blocks))
+    assert share <= 16 * 256 and min(blocks, 3) * (share * 76 + 2064) <= 160 * 1024
+
+
+def test_rule_outside_its_range(host):
+    for n in (0, 1, 65535, 9 * 65536 + 1, 20 * 65536 + 5, 2**40):
+        assert host.per_cu(n, 1000) == 0
 
 
 def inward_and_outward(m, n, formulation):
