@@ -127,7 +127,7 @@ def main():
     # timed region, cached), which the integrate calls below take through block = 0
     if args.block == 0:
         from paper_1803_08320_amd import autotune
-        shape_block = autotune.integrate_shape(s0, st, h)[0]
+        shape_block = autotune.integrate_shape(s0, st, h)[0] or 256  # 0: the library's default
     else:
         shape_block = args.block
 
@@ -742,7 +742,7 @@ def extra_legs(m, torch, np):
                     "status_counts": [int(x) for x in torch.bincount(st, minlength=6).cpu()]}
     out["camera_persistent"]["speedup_vs_plain"] = (out["camera_persistent"]["lane_steps_per_s"] /
                                                     out["camera_plain"]["lane_steps_per_s"])
-    out["camera_persistent"]["launch_shape"] = {"block": cam_shape[0], "steps_per_chunk": cam_shape[1],
+    out["camera_persistent"]["launch_shape"] = {"block": cam_shape[0] or 256, "steps_per_chunk": cam_shape[1] or 32,
                                                 "source": "autotuned"}
 
     # mixed-spin batch: 16 spins a_k = 0.99 k / 15 x 262,144 lanes, FP32 compensated state,

@@ -292,7 +292,8 @@ def integrate(state: torch.Tensor, status: torch.Tensor, steps: torch.Tensor, sp
     "christoffel": state = (x^mu, u^mu); "hamiltonian": state = (x^mu, p_mu), see
     convert_state.  block = 0 (and, for a persistent launch, steps_per_chunk = 0) takes
     the autotuner's cached launch shape for this kind of batch when there is one
-    (autotune.integrate_shape), else the library's defaults."""
+    (autotune.integrate_shape), else the library's defaults (also for lane counts that these may
+    launch in turns)."""
     n = state.shape[-1]
     prec = {"f64": F64, "f32k": F32_KAHAN}[precision]
     form = {"christoffel": FORM_CHRISTOFFEL, "hamiltonian": FORM_HAMILTONIAN}[formulation]
@@ -300,7 +301,8 @@ def integrate(state: torch.Tensor, status: torch.Tensor, steps: torch.Tensor, sp
     if block == 0 and checkpoint_every == 0 and state.is_cuda:
         from . import autotune
         shape = autotune.lookup_integrate(n, len(sts), precision, formulation, persistent)
-        if shape:
+        launch_steps = n_steps if persistent or steps_per_chunk == 0 else min(n_steps, steps_per_chunk)
+        if shape and shape[0] and not autotune.default_is_better(n, launch_steps, precision, persistent):
             block = shape[0]
             if persistent and steps_per_chunk == 0:
                 steps_per_chunk = shape[1]
