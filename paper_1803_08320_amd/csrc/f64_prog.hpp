@@ -58,7 +58,7 @@ __device__ __forceinline__ int32_t run_steps(const Spacetime &S, const HamConst<
         step_f64<HAM, ZERO_A>(S, P, h, y, y1, sr);
         ++ks;
         if (!still_active_f64(S, r_escape, sr, y1)) st = terminate_f64(S, r_escape, sr, y1, accept);
-        if (st != kActive || ks >= n) {
+        if (st != kActive || ks == n) {
             if (accept) copy8(y, y1);
             return ks;
         }
@@ -66,7 +66,7 @@ __device__ __forceinline__ int32_t run_steps(const Spacetime &S, const HamConst<
         ++ks;
         accept = true;
         if (!still_active_f64(S, r_escape, sr, y)) st = terminate_f64(S, r_escape, sr, y, accept);
-        if (st != kActive || ks >= n) {
+        if (st != kActive || ks == n) {
             if (!accept) copy8(y, y1);
             return ks;
         }

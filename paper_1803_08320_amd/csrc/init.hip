@@ -171,9 +171,9 @@ __device__ __forceinline__ Draw draw_attempt(const malbec_ic_spec &P, uint64_t l
 }
 
 // R(r) >= 0 and Theta(theta) >= 0.  The sign of Theta comes from Theta sin^2 theta (no division) where that is
-// clear of its own rounding and of that of sincos_any (whose reduction holds for |theta| < 1e6 and whose
-// sin or cos loses relative accuracy next to a multiple of pi/2); elsewhere from the expression that the
-// lane's state is formed with, so that a draw on the boundary is decided as its state will have it.
+// clear of its own rounding and of that of sincos_any (1e-16 of the terms without their factor cos^2;
+// its reduction holds for |theta| < 1e6), elsewhere from the expression that the lane's state is formed
+// with, so that a draw on the boundary is decided as its state will have it.
 // big_theta: a range beyond sincos_any.
 __device__ __forceinline__ bool admissible(const malbec_ic_spec &P, double M, double a, const Draw &D,
                                            bool big_theta)
@@ -188,7 +188,7 @@ __device__ __forceinline__ bool admissible(const malbec_ic_spec &P, double M, do
         const double Qs = D.Q * s2, k = a * a * (P.mu2 - D.E * D.E) * s2;
         const double T = Qs - c2 * (k + LL);
         ok = T > 0.0;
-        close = !(fabs(T) > 1e-12 * (fabs(Qs) + c2 * (fabs(k) + LL))) || !(fmin(s2, c2) > 1e-10);
+        close = !(fabs(T) > 1e-10 * (fabs(Qs) + (fabs(k) + LL)));
     }
     if (close) {
         sincos(D.th, &s, &c);

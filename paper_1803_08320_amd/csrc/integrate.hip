@@ -68,9 +68,10 @@ __global__ void __launch_bounds__(256) rk4_f64_kernel(IntArgs A, StTable T)
 #pragma unroll
     for (int k = 0; k < 8; ++k) y[k] = A.state[k * A.n + i];
     const HamConst<double> P = ham_const(S.a, y[4], y[7]);
+    int32_t taken = 0;
     if (!CKPT && st == kActive) {
         // a launch always has n_steps >= 1 (the launcher makes none for a call of zero steps)
-        const int32_t taken = run_steps<HAM, ZERO_A>(S, P, A.h, A.r_escape, A.n_steps, y, st);
+        taken = run_steps<HAM, ZERO_A>(S, P, A.h, A.r_escape, A.n_steps, y, st);
         // the lane's index rebuilt from wave-uniform values and its position in the
         // wavefront: no per-lane address stays live across the loop
         const int64_t ie = (int64_t)blockIdx.x * blockDim.x + wave0 +
@@ -79,9 +80,9 @@ __global__ void __launch_bounds__(256) rk4_f64_kernel(IntArgs A, StTable T)
         for (int k = 0; k < 8; ++k) A.state[k * A.n + ie] = y[k];
         A.status[ie] = st;
         A.steps[ie] += taken;
-    } else if (CKPT) {
+    } else if (CKPT || st == kActive) {  // (without CKPT never: the other instances keep their registers)
         const bool was_active = st == kActive;
-        const int32_t taken = run_checkpointed(
+        taken = run_checkpointed(
             A.k0, A.n_steps, A.ck_every, A.ck_last, was_active,
             [&](int32_t m, bool &active) {
                 const int32_t ks = run_steps<HAM>(S, P, A.h, A.r_escape, m, y, st);
