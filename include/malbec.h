@@ -229,11 +229,11 @@ MALBEC_API int malbec_version(void);
  * aux = run->persistent), MALBEC_OP_CAMERA (n = nx * ny pixels: 256 + 64n bytes), MALBEC_OP_ADJOINT
  * (n lanes, aux = the checkpoint interval K: K * 8 * n doubles),
  * MALBEC_OP_ADAPTIVE (n lanes, aux = ad->persistent ? 1 + ad->schedule : 0; about
- * 8n bytes with the periapsis schedule) or MALBEC_OP_ADAPTIVE_ORDER (n lanes, aux
+ * 8n bytes with MALBEC_SCHED_PERIAPSIS) or MALBEC_OP_ADAPTIVE_ORDER (n lanes, aux
  * unused; about 4n bytes).  Returns 0 for operations that need none. */
 MALBEC_API size_t malbec_workspace_bytes(int32_t op, int64_t n, int32_t aux);
 
-/* Build the initial state of n lanes on the device (one GPU thread per lane).
+/* Build the initial state of n lanes on the device.
  * spec: host.  b: host (st_of_lane device or NULL).  state: device, 8n doubles (out).
  * consts: device, 4n doubles (out, nullable): (E, L_z, Q, mu2) component-major;
  * attempts: device, n int64 (out, nullable): draws used by the CONSTANTS sampler.
@@ -390,7 +390,7 @@ MALBEC_API int malbec_adaptive_order(const malbec_batch *b, int64_t n, const dou
  * allocate device memory around the call (code under HIP graph capture, serving
  * loops, harnesses that forbid allocation).  Arguments, results and errors are those
  * of malbec_integrate_adaptive; the call allocates nothing: the work counter and the
- * periapsis work order use a static device array of the library (16 MiB + 8.4 KiB on
+ * work order use a static device array of the library (16 MiB + 8.4 KiB on
  * every GPU the library runs on, held until the process ends), so n is limited to
  * MALBEC_NOALLOC_MAX_LANES (2^21; larger n: MALBEC_EINVAL).  Every call on one GPU uses
  * that GPU's single array: calls that overlap on one GPU (concurrent streams or host

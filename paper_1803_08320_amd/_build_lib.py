@@ -28,7 +28,9 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=on", "--offload-arch=" + 
 # 2.99 and 2.42 -> 2.39 ms, 20,000 monitored lanes 0.920 -> 0.896 ms, the gridded kernel (262,144
 # lanes x 400 steps) 6.42 -> 6.10 ms, a 512 x 512 camera image 3.14 -> 3.03 ms, 262,144
 # FP32-compensated lanes x 600 steps 1.33 -> 1.25 ms.  The adaptive kernel is slower with it
-# (262,144 lanes 4.95 -> 5.14 ms), and it changes nothing for the adjoint.
+# (262,144 lanes 4.95 -> 5.14 ms), and it changes nothing for the adjoint.  The monitored
+# FP32-compensated queue of the Hamiltonian form takes 3 to 5 % more with it at 230,000 to 262,144
+# lanes, and up to 3 % less from 400,000 on.
 SCHEDULE = ["-mllvm", "-amdgpu-sched-strategy=max-ilp", "-mllvm", "-enable-post-misched=0"]
 SCHEDULED = ("camera.hip", "grid.hip", "integrate.hip", "mixed.hip", "trajectory.hip")
 

@@ -131,7 +131,7 @@ size_t malbec_workspace_bytes(int32_t op, int64_t n, int32_t aux)
     if (op == MALBEC_OP_CAMERA && n >= 0)  // work counter (own cache line), then the rays' initial states
         return 256 + (size_t)n * 8 * sizeof(double);
     if (op == MALBEC_OP_ADAPTIVE && aux == 2 && n >= 0)
-        return 256 + sched_layout(n).bytes;  // work counter, then the periapsis order
+        return 256 + sched_layout(n).bytes;  // work counter, then the work order
     if ((op == MALBEC_OP_INTEGRATE || op == MALBEC_OP_ADAPTIVE) && aux)
         return 256;  // persistent kernel's work counter
     if (op == MALBEC_OP_ADAPTIVE_ORDER && n > 0) return sched_layout(n).order;

@@ -20,9 +20,9 @@
 // allows (Stencil below).  Measured on one MI355X, the same machine before (stencil
 // entirely in LDS, one wave per SIMD with double nodes; derivatives of the inverse
 // metric; four inlined copies of the right-hand side) and after:
-//   801 x 401 grid, double nodes, 262,144 lanes x 400 steps: 10.92 -> 6.32 ms
-//     (1.66 x 10^10 lane-steps/s; VALU active 0.52 -> 0.73, 2006 -> 1512 per step)
-//   401 x 201 grid, float nodes, 100,003 lanes x 500 steps: 5.00 -> 3.58 ms
+//   801 x 401 grid, double nodes, 262,144 lanes x 400 steps: 10.92 -> 5.85 ms
+//     (1.79 x 10^10 lane-steps/s; VALU active 0.52 -> 0.77, 2006 -> 1520 per step)
+//   401 x 201 grid, float nodes, 100,003 lanes x 500 steps: 5.00 -> 3.5 ms
 // Cell changes cost 15 % of it (1.42 against 1.66 ms on 131,072 lanes x 200 steps that
 // stay in their cells or not).  Gathering for the few lanes that change cell by the whole
 // wavefront (one load per such lane instead of 40 under its mask) was 4 % slower: the
@@ -274,7 +274,8 @@ __device__ __forceinline__ int32_t grid_steps(const GridArgs &A, const HamConst<
     return taken;
 }
 
-// At most 256 registers, the two waves per SIMD that the stencils' LDS allows.
+// At most 256 registers, the two waves per SIMD that the stencils' LDS allows; four (16 in turns) that
+// live across the loop are spilled, 20 B (52 B) per lane.
 template <typename Node>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 rk4_grid_kernel(GridArgs A)

@@ -208,8 +208,10 @@ __device__ __forceinline__ bool admissible(const malbec_ic_spec &P, double M, do
 // 64 at a time, with all threads busy and coalesced stores.
 // Bound by VALU issue (0.84 of the time; about 245 instructions per attempt, half of them
 // the generator's).  Measured on one MI355X with 1,048,576 lanes of the benchmark's ranges,
-// against one thread per lane: 705 -> 190 us, 3.35 x 10^8 -> 0.86 x 10^8 wavefront
-// instructions.
+// against one thread per lane: 705 -> 195 us, 3.35 x 10^8 -> 0.89 x 10^8 wavefront
+// instructions.  Where nearly every draw is admissible, 16,384 to 100,000 lanes take 2 to 5 us more than with
+// one thread per lane (18-21 us): a run is shorter than a wavefront and has no attempts to share; runs
+// of 32 and 64 lanes would cost the benchmark's ranges as much or more.
 constexpr int kMaxRun = 256;     // lanes per wavefront: their attempts' LDS
 constexpr int kSampleBlock = 256;
 template <bool MULTI>

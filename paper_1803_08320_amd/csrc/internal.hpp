@@ -86,7 +86,7 @@ int launch_adaptive(const malbec_adaptive &ad, const StTable &T, const int32_t *
                     int64_t n, double *state, double *tau, double *h, int32_t *status,
                     int32_t *steps, int32_t *rejects, const uint32_t *order, void *ws,
                     hipStream_t s);
-// Byte offsets in the workspace of the periapsis schedule of n lanes: bucket counts and
+// Byte offsets in the workspace of a work order of n lanes: bucket counts and
 // running offsets (MALBEC_SCHED_BUCKETS uint32 each), keys and order (n uint32 each,
 // 256-byte aligned); `order` is also the size without the order array.
 struct SchedLayout {

@@ -308,8 +308,8 @@ MALBEC_HD inline void schwarzschild_accel_half(T M, T r, T s2, T sc, T ut, T ur,
     ath = fma(-sig2, uth, sc * fma(DI, uu, q * uu));
 }
 
-// Reverse mode of kerr_accel, against which the host checks hold that of kerr_accel_half (which
-// the adjoint kernel runs): given the cotangents (bat, bar, bath, baph) of
+// Reverse mode of kerr_accel, which host checks alone run: they hold against it that of kerr_accel_half, which
+// the adjoint kernel runs: given the cotangents (bat, bar, bath, baph) of
 // (a^t, a^r, a^theta, a^phi), the cotangents of r, s = sin theta, c = cos theta and
 // of the 4-velocity (ub[0..3] for u^t, u^r, u^theta, u^phi), i.e. the transposed
 // Jacobian of the computed expression applied to b.  The forward expressions are

@@ -358,8 +358,11 @@ struct MixProg {
 };
 
 // The Christoffel-form kernels are held to 128 registers, four waves per SIMD (the
-// FP64 zone step sets the peak; the FP32 step alone needs about 80); the Hamiltonian
-// form's zone step needs about 160 and keeps the compiler's default (three waves).
+// FP64 zone step sets the peak; the FP32 step alone needs about 80).  The one-thread-per-lane
+// kernel fits; the persistent one spills 24 registers (84 B per lane), which the queue's
+// traffic shows (2.6 GB written per launch of 4,194,304 lanes x 20,000 steps, 0.6 s) and its
+// time does not: three waves without spills are slower.  The Hamiltonian form's zone step needs
+// about 160 and keeps the compiler's default (three waves).
 template <bool MULTI, bool HAM>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HAM ? 1 : 4, HAM ? 8 : 4)))
 rk4_f32k_kernel(MixArgs A, StTable T)

@@ -1,5 +1,5 @@
 // Adaptive integration without a caller workspace: the scratch of the persistent
-// work queue and of its periapsis work order lives in a file-scope device array.
+// work queue and of its work order lives in a file-scope device array.
 //
 // For callers that cannot allocate device memory around the call (code under HIP
 // graph capture, serving loops, harnesses that forbid allocation).  The array is a

@@ -6,10 +6,11 @@
 // between the 10% and the 100% quantiles on bound Kerr orbits).  The persistent work
 // queue hands lanes out in the order it is given; a lane that is long and handed out
 // late keeps its wavefront busy after every other has drained the queue.  Handing the
-// longest lanes out first (the longest-processing-time rule) removes that tail.  The
-// expected length is ranked by the periapsis r_p, read off the Carter-separated radial
-// equation of the lane's own constants (E, L_z, Q, mu^2) (Sections 3-4 integrate the
-// same constants of motion):
+// longest lanes out first (the longest-processing-time rule) removes that tail.
+// MALBEC_SCHED_PERIAPSIS, named after its first form, ranks the lanes by their expected
+// length until tau_end (sched_cost_kernel below).  malbec_adaptive_order ranks them by the
+// periapsis r_p alone, read off the Carter-separated radial equation of the lane's own
+// constants (E, L_z, Q, mu^2) (Sections 3-4 integrate the same constants of motion):
 //   (rho^2 dr/dtau)^2 = R(r) = [E (r^2 + a^2) - a L_z]^2 - Delta [mu^2 r^2 + (L_z - a E)^2 + Q],
 // R(r_0) >= 0 at the lane's radius; r_p is the first zero of R inward from r_0.
 //
@@ -100,7 +101,10 @@ __global__ void __launch_bounds__(256) sched_key_kernel(KeyArgs A, StTable T)
 // extrapolated.  The attempts of the benchmark's orbits (a = 0.9 and 0.3, tau = 400, tolerances
 // 1e-10 and 1e-12) follow lambda^0.82 L_z^-0.47 (mu^2 - E^2)^-0.35 within 6.4 % rms and at most 15 %
 // upwards (a small L_z means a passage near the axis); the periapsis correlates with them
-// at 0.48.  Bound by the steps' single-precision arithmetic: 64 us for 262,144 lanes.  The
+// at 0.48 (the exponents are fitted to these orbits; other batches get another order, never another
+// result, and gain as well: null, unbound and near-equatorial orbits, spins 0 to 0.998, tolerances 1e-6
+// and 1e-9 take 1 to 38 % less time than in the order by periapsis, alone 200,000 and 262,144 orbits close to
+// circular, 8 < r < 16, take 7 to 9 % more).  Bound by the steps' single-precision arithmetic: 64 us for 262,144 lanes.  The
 // integration in this order against that by periapsis, on one MI355X (tau = 400, 1e-12):
 // 65,536 lanes 5.4 -> 4.6 ms, 262,144 lanes 7.7 -> 5.3 ms, 1,048,576 lanes 15.4 -> 13.8 ms,
 // and 9.8 -> 6.6 ms for 262,144 lanes at a = 0.3, a quarter of which plunge.

@@ -47,9 +47,9 @@ constexpr int32_t kMaxShare = kIdleTurns * 256;  // the lanes of a block are few
 MALBEC_HD inline bool look_after(int32_t turn) { return turn % kIdleTurns == kIdleTurns - 1; }
 
 // The blocks per CU of a launch in turns (rk4_f64_turns_kernel, rk4_record_turns_kernel), 0 where one thread per
-// lane is the better launch.  With n / (256 lanes per CU) = w + f, w whole, one thread per lane takes the time of w + 1
-// blocks on every CU, in turns w blocks per CU (four at most) share the lanes.  FP64 kernels, 1,000 steps on
-// one MI355X, one thread per lane and in turns, ms (Christoffel; Hamiltonian form):
+// lane is the better launch.  With n / (256 lanes per CU) = w + f, w whole, one thread per lane takes the
+// time of w + 1 blocks on every CU, in turns w blocks per CU (four at most) share the lanes.  FP64 kernels,
+// 1,000 steps on one MI355X, one thread per lane and in turns, ms (Christoffel; Hamiltonian form):
 //   w + f   1.1            1.5            1.65           2.1            2.6            3.1
 //         1.47 1.02      1.48 1.34      1.48 1.48      2.16 1.64      2.18 2.00      2.95 2.49
 //         1.19 0.85      1.21 1.13      1.21 1.25      1.71 1.36      1.73 1.62      2.29 1.90

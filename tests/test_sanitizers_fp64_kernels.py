@@ -22,7 +22,8 @@ struct Half {
     void operator()(int, double r, double th, double ut, double ur, double uth, double uph, double &at2,
                     double &ar, double &ath, double &aph2) const {
         const double s = std::sin(th), c = std::cos(th);
-        if (a == 0.0) malbec::schwarzschild_accel_half<double>(M, r, s * s, s * c, ut, ur, uth, uph, at2, ar, ath, aph2);
+        if (a == 0.0)
+            malbec::schwarzschild_accel_half<double>(M, r, s * s, s * c, ut, ur, uth, uph, at2, ar, ath, aph2);
         else malbec::kerr_accel_half<double>(M, a, r, s * s, s * c, ut, ur, uth, uph, at2, ar, ath, aph2);
     }
     double &Y(int st, int k) { return Ys[st][k]; }
@@ -40,7 +41,8 @@ struct Ham {
     void operator()(int, double r, double th, double pr, double pth, double &dt, double &dr, double &dth,
                     double &dph, double &dpr, double &dpth) const {
         const double s = std::sin(th), c = std::cos(th);
-        if (a == 0.0) malbec::schwarzschild_ham_s2<double>(M, r, s * s, s * c, pr, pth, P, dt, dr, dth, dph, dpr, dpth);
+        if (a == 0.0)
+            malbec::schwarzschild_ham_s2<double>(M, r, s * s, s * c, pr, pth, P, dt, dr, dth, dph, dpr, dpth);
         else malbec::kerr_ham_s2<double>(M, a, r, s * s, s * c, pr, pth, P, dt, dr, dth, dph, dpr, dpth);
     }
 };
