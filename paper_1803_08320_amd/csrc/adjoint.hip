@@ -19,6 +19,7 @@
 // A training step of 65,536 lanes x 1,024 steps (forward, backward) with the transposed
 // Jacobian of kerr_accel 5.36 ms, with that of kerr_accel_half 5.02; 20,000 lanes x 512 steps
 // 2.46 and 2.30 (one MI355X, the same machine before and after).
+#include "checkpoint.hpp"
 #include "dual.hpp"
 #include "internal.hpp"
 
@@ -101,7 +102,7 @@ __global__ void __launch_bounds__(256) adjoint_kernel(AdjArgs A, StTable T)
 #pragma unroll
     for (int k = 0; k < 8; ++k) lam[k] = bad ? __builtin_nan("") : A.g_final[k * n + i];
 
-    const int32_t nseg = (A.N + A.K - 1) / A.K;
+    const int32_t nseg = checkpoint_segments(A.N, A.K);
     for (int32_t s = nseg - 1; s >= 0 && !bad; --s) {
         const int32_t g0 = s * A.K;
         if (g0 >= taken) continue;  // the lane had stopped before this segment

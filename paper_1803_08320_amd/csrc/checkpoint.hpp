@@ -35,4 +35,7 @@ MALBEC_HD inline int32_t run_checkpointed(int32_t k0, int32_t n_steps, int32_t e
     return taken;
 }
 
+// The segments between the slots of a call of n_steps >= 1 steps, for the walk back.
+MALBEC_HD inline int32_t checkpoint_segments(int32_t n_steps, int32_t every) { return (n_steps - 1) / every + 1; }
+
 }  // namespace malbec

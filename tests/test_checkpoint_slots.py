@@ -13,6 +13,7 @@ MAX = 2**31 - 1
 
 SRC = r"""
 #include "checkpoint.hpp"
+extern "C" int32_t segments(int32_t n_steps, int32_t every) { return malbec::checkpoint_segments(n_steps, every); }
 // A lane that stops after `stop` steps of the call, from launch to launch of `chunk` steps.  put_at[s]
 // receives the step whose state slot s holds.  Returns the steps taken, negative: a run of no steps or
 // of more than the launch has left, or a slot outside the call's.
@@ -75,6 +76,12 @@ def test_slots_of_the_longest_calls(host, every, n_steps, chunk):
         at = (C.c_int64 * slots)(*[-1] * slots)
         assert host.walk(n_steps, chunk, every, stop, at) == min(stop, n_steps)
         assert list(at) == [min(s * every, stop) for s in range(slots)]
+
+
+@pytest.mark.parametrize("every", [1, 2, 50, 99, 100, 101, 2**30, MAX - 99, MAX])
+def test_segments_of_the_walk_back(host, every):
+    for n_steps in (1, 2, 100, MAX - 1, MAX):
+        assert host.segments(n_steps, every) == -(-n_steps // every)
 
 
 @pytest.mark.gpu
